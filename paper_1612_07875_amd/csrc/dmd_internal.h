@@ -147,7 +147,7 @@ struct SolveArgs {
                            // dimension m (rows past the window's columns zero)
     double* At;            // r x r (complex: interleaved)
     double* W;             // r x r complex
-    double* work;          // global scratch: 4 M (M+1) values (A, V, Q or Z, tail scratch)
+    double* work;          // global scratch: solve_work_doubles (Jacobi: A, V, Q; tridiagonal: T, reflectors)
     double* Vfull;         // m x m eigenvectors of the latest solve, sigma order
     void* Bphi;            // m x 2r coefficients of Phi (row-major, data precision)
     void* Bpod;            // m x r (real) or m x 2r (complex) coefficients of U
@@ -163,6 +163,12 @@ struct SolveArgs {
     void* snap_B;
     int snap_n16;
 };
+constexpr int kTridPad = 8;
+// Doubles of a solve's workspace.
+inline size_t solve_work_doubles(int m, int cplx) {
+    const size_t M = m + (m & 1);
+    return (cplx ? 2 : 1) * 4 * M * (M + 1) + 2 * kTridPad + 128;
+}
 hipError_t launch_solve_sym(const SolveArgs& a, hipStream_t s);
 // Same outputs by Householder tridiagonalization, multisection and twisted
 // factorizations (no warm start).
@@ -171,15 +177,19 @@ hipError_t launch_solve_trid(const SolveArgs& a, hipStream_t s);
 // real tridiagonal solve of the new window as one launch.
 hipError_t launch_finalize_solve_trid(double* G, const double* partials, int nblk, const SolveArgs& a,
                                       hipStream_t s);
-// Grouped real symmetric solves (one workgroup per item; lds: m <= 64) by
-// Jacobi or by the tridiagonal method, and the grouped eig of A~.
+// Grouped real symmetric solves by Jacobi (one workgroup per item; lds:
+// m <= 64) or by the tridiagonal method, and the grouped eig of A~.
 hipError_t launch_jacobi_grouped(const SolveArgs* items_lds, int n_lds, const SolveArgs* items_glb, int n_glb,
                                  hipStream_t s);
-hipError_t launch_trid_grouped(const SolveArgs* items_lds, int n_lds, const SolveArgs* items_glb, int n_glb,
-                               hipStream_t s);
-// Grouped Hermitian (complex) tridiagonal solves: items_lds m <= 32, items_glb m > 32.
-hipError_t launch_trid_grouped_cplx(const SolveArgs* items_lds, int n_lds, const SolveArgs* items_glb, int n_glb,
-                                    hipStream_t s);
+// The tridiagonal solves come in three size classes (trid_class), each with a
+// list of its own: items[c] holds count[c] windows of class c.
+int trid_class(int m, int cplx);
+hipError_t launch_trid_grouped(const SolveArgs* const items[3], const int count[3], hipStream_t s);
+// Grouped Hermitian (complex) tridiagonal solves.
+hipError_t launch_trid_grouped_cplx(const SolveArgs* const items[3], const int count[3], hipStream_t s);
+// Hermitian windows of more than 128 columns, one workgroup each (matrix in
+// the workspace): one window by value, or n items.
+hipError_t launch_solve_trid_wide(const SolveArgs* one, const SolveArgs* items, int n, hipStream_t s);
 hipError_t launch_eig_grouped(const SolveArgs* items, int n, hipStream_t s);
 hipError_t launch_solve_eig(const SolveArgs& a, hipStream_t s);
 

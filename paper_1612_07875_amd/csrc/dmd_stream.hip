@@ -365,9 +365,8 @@ struct SetSizes {
 };
 SetSizes set_sizes(const dmd_stream* h) {
     const size_t cw = h->cplx ? 2 : 1, m = h->m, r = h->r;
-    const size_t M = m + (m & 1);
     const size_t coef = h->coef_f64 ? 8 : 4;
-    return SetSizes{cw * m * r, cw * r * r, 2 * r * r, cw * 4 * M * (M + 1), cw * m * m, coef * 2 * m * r,
+    return SetSizes{cw * m * r, cw * r * r, 2 * r * r, dmd::solve_work_doubles(h->m, h->cplx), cw * m * m, coef * 2 * m * r,
                     coef * cw * m * r};
 }
 
@@ -618,7 +617,6 @@ int create_impl(int64_t n, int32_t m, int32_t r, const dmd_opts_t* opts, dmd_str
 
     int rc = DMD_OK;
     const int cw = h->cplx ? 2 : 1;
-    const int M = m + (m & 1);
     h->nblk_cap = dmd::gram_push_blocks(n, h->elem_bytes);
     const size_t coef = h->coef_f64 ? 8 : 4;
 #define ALLOC(p, bytes)                                  \
@@ -653,7 +651,7 @@ int create_impl(int64_t n, int32_t m, int32_t r, const dmd_opts_t* opts, dmd_str
     ALLOC(h->V, sizeof(double) * cw * (size_t)m * r);
     ALLOC(h->At, sizeof(double) * cw * (size_t)r * r);
     ALLOC(h->W, sizeof(double) * 2 * (size_t)r * r);
-    ALLOC(h->work, sizeof(double) * cw * 4 * (size_t)M * (M + 1));
+    ALLOC(h->work, sizeof(double) * dmd::solve_work_doubles(m, h->cplx));
     ALLOC(h->Vfull, sizeof(double) * cw * (size_t)m * m);
     ALLOC(h->Bphi, coef * 2 * (size_t)m * r);
     if (!h->cplx) {
@@ -963,8 +961,11 @@ DMD_API int dmd_stream_push_block(dmd_stream_t* h, const void* X_new, int64_t ld
     if (h->opts.auto_solve) {
         const dmd::SolveArgs* t = h->solve_tbl + (h->kmax - k);
         const bool lds = h->m + (h->m & 1) <= 64;
+        const dmd::SolveArgs* const lists[3] = {t, t, t};
+        int count[3] = {0, 0, 0};
+        count[dmd::trid_class(h->m, 0)] = k;
         HIP_TRY(timed("block_solve", s, [&] {
-            hipError_t e = h->use_trid ? dmd::launch_trid_grouped(t, lds ? k : 0, t, lds ? 0 : k, s)
+            hipError_t e = h->use_trid ? dmd::launch_trid_grouped(lists, count, s)
                                        : dmd::launch_jacobi_grouped(t, lds ? k : 0, t, lds ? 0 : k, s);
             return e != hipSuccess ? e : dmd::launch_eig_grouped(t, k, s);
         }));
@@ -1701,7 +1702,7 @@ namespace {
 // copied to the device before the grouped launches (two copies alternate so
 // that the host never overwrites a table a tick in flight still reads).
 struct TickLayout {
-    size_t gram, gblk, lds, glb, tlds, tglb, clds, cglb, all, proj, pblk, bytes;
+    size_t gram, gblk, lds, glb, trid[3], ctrid[3], all, proj, pblk, bytes;
     static TickLayout make(int cap) {
         TickLayout L;
         auto al = [](size_t x) { return (x + 255) / 256 * 256; };
@@ -1709,11 +1710,13 @@ struct TickLayout {
         L.gblk = al(L.gram + sizeof(dmd::GramItem) * cap);
         L.lds = al(L.gblk + sizeof(int) * (cap + 1));
         L.glb = al(L.lds + sizeof(dmd::SolveArgs) * cap);
-        L.tlds = al(L.glb + sizeof(dmd::SolveArgs) * cap);
-        L.tglb = al(L.tlds + sizeof(dmd::SolveArgs) * cap);
-        L.clds = al(L.tglb + sizeof(dmd::SolveArgs) * cap);
-        L.cglb = al(L.clds + sizeof(dmd::SolveArgs) * cap);
-        L.all = al(L.cglb + sizeof(dmd::SolveArgs) * cap);
+        size_t at = al(L.glb + sizeof(dmd::SolveArgs) * cap);
+        for (size_t* l : {L.trid, L.ctrid})
+            for (int c = 0; c < 3; ++c) {
+                l[c] = at;
+                at = al(at + sizeof(dmd::SolveArgs) * cap);
+            }
+        L.all = at;
         L.proj = al(L.all + sizeof(dmd::SolveArgs) * cap);
         L.pblk = al(L.proj + sizeof(dmd::ProjectArgs) * cap);
         L.bytes = al(L.pblk + sizeof(int) * (cap + 1));
@@ -1727,10 +1730,10 @@ struct TickLayout {
 // and on the descriptor buffer, everything else reaches the kernels through
 // the descriptors that the graph's first node copies from pinned memory.
 struct TickShape {
-    int buf, count, nl, ng, ntl, ntg, gtot, np, ptot;
+    int buf, count, nl, ng, nt[3], gtot, np, ptot;
     bool operator==(const TickShape& o) const {
-        return buf == o.buf && count == o.count && nl == o.nl && ng == o.ng && ntl == o.ntl && ntg == o.ntg &&
-               gtot == o.gtot && np == o.np && ptot == o.ptot;
+        return buf == o.buf && count == o.count && nl == o.nl && ng == o.ng && nt[0] == o.nt[0] && nt[1] == o.nt[1] &&
+               nt[2] == o.nt[2] && gtot == o.gtot && np == o.np && ptot == o.ptot;
     }
 };
 struct TickGraph {
@@ -1930,14 +1933,11 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
     int* gblk = reinterpret_cast<int*>(H + b->L.gblk);
     auto* sl = reinterpret_cast<dmd::SolveArgs*>(H + b->L.lds);
     auto* sg = reinterpret_cast<dmd::SolveArgs*>(H + b->L.glb);
-    auto* tl = reinterpret_cast<dmd::SolveArgs*>(H + b->L.tlds);
-    auto* tg = reinterpret_cast<dmd::SolveArgs*>(H + b->L.tglb);
-    auto* cl = reinterpret_cast<dmd::SolveArgs*>(H + b->L.clds);
-    auto* cg = reinterpret_cast<dmd::SolveArgs*>(H + b->L.cglb);
     auto* sa = reinterpret_cast<dmd::SolveArgs*>(H + b->L.all);
     auto* pa = reinterpret_cast<dmd::ProjectArgs*>(H + b->L.proj);
     int* pblk = reinterpret_cast<int*>(H + b->L.pblk);
-    int na = 0, nl = 0, ng = 0, ntl = 0, ntg = 0, ncl = 0, ncg = 0, np = 0, gtot = 0, ptot = 0;
+    int na = 0, nl = 0, ng = 0, np = 0, gtot = 0, ptot = 0;
+    int nt[3] = {0, 0, 0}, nc[3] = {0, 0, 0};  // tridiagonal solves by size class, real and Hermitian
     std::vector<int> own;  // members that run their own Gram and projection kernels
     for (int i = 0; i < count; ++i) {
         dmd_stream* h = streams[i];
@@ -1972,18 +1972,14 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
         dmd::SolveArgs a;
         fill_solve_args(h, a);
         sa[i] = a;
-        if (h->cplx) {
-            if (h->m <= 32) cl[ncl++] = a;
-            else cg[ncg++] = a;
+        if (h->use_trid) {
+            const int c = dmd::trid_class(h->m, h->cplx);
+            const size_t off = h->cplx ? b->L.ctrid[c] : b->L.trid[c];
+            reinterpret_cast<dmd::SolveArgs*>(H + off)[h->cplx ? nc[c]++ : nt[c]++] = a;
+        } else if (h->m + (h->m & 1) <= 64) {
+            sl[nl++] = a;
         } else {
-            const bool small = h->m + (h->m & 1) <= 64;
-            if (h->use_trid) {
-                if (small) tl[ntl++] = a;
-                else tg[ntg++] = a;
-            } else {
-                if (small) sl[nl++] = a;
-                else sg[ng++] = a;
-            }
+            sg[ng++] = a;
         }
     }
     gblk[na] = gtot;
@@ -2042,12 +2038,13 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
         e = phase("batch_solve", [&] {
             hipError_t f = dmd::launch_jacobi_grouped(reinterpret_cast<const dmd::SolveArgs*>(D + b->L.lds), nl,
                                                       reinterpret_cast<const dmd::SolveArgs*>(D + b->L.glb), ng, q);
-            if (f == hipSuccess)
-                f = dmd::launch_trid_grouped(reinterpret_cast<const dmd::SolveArgs*>(D + b->L.tlds), ntl,
-                                             reinterpret_cast<const dmd::SolveArgs*>(D + b->L.tglb), ntg, q);
-            if (f == hipSuccess)
-                f = dmd::launch_trid_grouped_cplx(reinterpret_cast<const dmd::SolveArgs*>(D + b->L.clds), ncl,
-                                                  reinterpret_cast<const dmd::SolveArgs*>(D + b->L.cglb), ncg, q);
+            const dmd::SolveArgs *rl[3], *cl[3];
+            for (int c = 0; c < 3; ++c) {
+                rl[c] = reinterpret_cast<const dmd::SolveArgs*>(D + b->L.trid[c]);
+                cl[c] = reinterpret_cast<const dmd::SolveArgs*>(D + b->L.ctrid[c]);
+            }
+            if (f == hipSuccess) f = dmd::launch_trid_grouped(rl, nt, q);
+            if (f == hipSuccess) f = dmd::launch_trid_grouped_cplx(cl, nc, q);
             if (f == hipSuccess)
                 f = dmd::launch_eig_grouped(reinterpret_cast<const dmd::SolveArgs*>(D + b->L.all), count, q);
             return f;
@@ -2065,7 +2062,7 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
     // with kernels of their own pass their frames as launch arguments, so
     // such ticks run eagerly
     if (b->graphs > 0 && own.empty()) {
-        const TickShape shape{buf, count, nl, ng, ntl, ntg, gtot, np, ptot};
+        const TickShape shape{buf, count, nl, ng, {nt[0], nt[1], nt[2]}, gtot, np, ptot};
         TickGraph* tg = nullptr;
         for (TickGraph& g : b->tick_graphs)
             if (g.shape == shape) tg = &g;

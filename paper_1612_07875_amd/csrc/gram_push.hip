@@ -77,13 +77,13 @@ __device__ __forceinline__ void load_slab(const T* __restrict__ col, int64_t bas
 __global__ __launch_bounds__(kFinThreads)
 void k_gram_finalize(double* __restrict__ G, const double* __restrict__ partials, int nblk, int m, int slots,
                      DevState* __restrict__ st) {
-    gram_finalize_body(G, partials, nblk, m, slots, st);
+    gram_finalize_body<kFinThreads>(G, partials, nblk, m, slots, st);
 }
 
 __global__ __launch_bounds__(kFinThreads)
 void k_gram_finalize_grouped(const GramItem* __restrict__ items) {
     const GramItem& g = items[blockIdx.x];
-    gram_finalize_body(g.G, g.partials, g.nblk, g.m, g.slots, g.st);
+    gram_finalize_body<kFinThreads>(g.G, g.partials, g.nblk, g.m, g.slots, g.st);
 }
 
 // One workgroup per slab of kThreads * N * ITER consecutive elements.

@@ -20,62 +20,10 @@
 //     mode argmin |log lambda| (Algorithm 3);
 //   * DMD coefficients C = V Sigma^-1 W for the projection Phi = X' C (Eq. Phi)
 //     and the background coefficients C[:, bg] b_bg lambda_bg^m.
-#include <cfloat>
-
-#include "cplx.h"
-#include "dmd_internal.h"
-#include "gram_finalize.h"
+#include "solve_common.h"
 
 namespace dmd {
 namespace {
-
-constexpr int kRMax = 32;         // largest truncation rank handled by k_solve_eig
-constexpr double kEps = DBL_EPSILON;
-
-// acc + sum of fa(k) * fb(k) over k = k0, k0 + step, ... < L, added in that
-// order.  The operands of U consecutive terms are read before their
-// products, so that their memory latencies overlap: a loop that reads,
-// waits and multiplies one term at a time pays a full round trip per term,
-// which the workspace forms of the solves (matrix and coefficients in
-// global memory) cannot afford.  The sum is the plain loop's, bit for bit.
-// U = 1 is the plain loop (the LDS forms: their register count decides
-// whether a solve fits beside a running projection).
-template <int U, typename S, typename FA, typename FB>
-__device__ __forceinline__ S ordered_dot(S acc, int k0, int step, int L, FA fa, FB fb) {
-    int k = k0;
-    if constexpr (U > 1) {
-        for (; k + (U - 1) * step < L; k += U * step) {
-            S x[U], y[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                x[u] = fa(k + u * step);
-                y[u] = fb(k + u * step);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) acc = acc + mulr(x[u], y[u]);
-        }
-    }
-    for (; k < L; k += step) acc = acc + mulr(fa(k), fb(k));
-    return acc;
-}
-// terms read ahead by the workspace forms: 8 real or 4 complex values
-template <typename S, bool LDS> constexpr int kAhead = LDS ? 1 : (sizeof(S) == sizeof(double) ? 8 : 4);
-
-template <typename S> __device__ __forceinline__ S gram_at(const double* G, int a, int b, int slots);
-template <> __device__ __forceinline__ double gram_at<double>(const double* G, int a, int b, int slots) {
-    return G[a + (int64_t)b * slots];
-}
-template <> __device__ __forceinline__ cplx gram_at<cplx>(const double* G, int a, int b, int slots) {
-    const double* p = G + 2 * (a + (int64_t)b * slots);
-    return cplx{p[0], p[1]};
-}
-
-template <typename S> __device__ __forceinline__ void store_s(double* out, int64_t i, S v);
-template <> __device__ __forceinline__ void store_s<double>(double* out, int64_t i, double v) { out[i] = v; }
-template <> __device__ __forceinline__ void store_s<cplx>(double* out, int64_t i, cplx v) {
-    out[2 * i] = v.re;
-    out[2 * i + 1] = v.im;
-}
 
 // Round-robin tournament: in round `rd` (0 .. M-2) pair i (0 .. M/2-1) is (p, q);
 // every index appears in exactly one pair per round and every pair of indices
@@ -93,80 +41,6 @@ __device__ __forceinline__ void rr_pair(int rd, int i, int M, int& p, int& q) {
     }
 }
 
-// 1/sqrt(x) to full FP64 accuracy: hardware estimate plus two Newton steps
-// (the estimate carries ~23 correct bits).  Dependent FP64 operations cost
-// ~32 cycles each here, so this replaces the longer correctly-rounded
-// sqrt/division sequences on the latency-bound paths.
-__device__ __forceinline__ double rsqrt_acc(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * x;
-    double e = fma(-h * y, y, 0.5);
-    y = fma(y, e, y);
-    e = fma(-h * y, y, 0.5);
-    return fma(y, e, y);
-}
-// 1/x to ~46 bits (estimate plus one Newton step).
-__device__ __forceinline__ double rcp_fast(double x) {
-    const double y = __builtin_amdgcn_rcp(x);
-    return fma(y, fma(-x, y, 1.0), y);
-}
-// 1/x to full FP64 accuracy (estimate plus two Newton steps).
-__device__ __forceinline__ double rcp_acc(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-    y = fma(y, fma(-x, y, 1.0), y);
-    return fma(y, fma(-x, y, 1.0), y);
-}
-
-// A double from another lane of the same 16-lane row, by a DPP lane pattern
-// (a register move, no trip through the LDS crossbar as __shfl_xor takes).
-template <int CTRL> __device__ __forceinline__ double dpp_f64(double x) {
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b & 0xffffffffull), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
-    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-// Sum over each aligned group of G lanes (G = 1, 2, 4, .., 64; every lane of
-// the group active), the same value in every lane of the group: neighbour
-// pairs, then pairs of pairs (quad permutations 1,0,3,2 and 2,3,0,1); then
-// the mirror of each 8-lane half-row and of each 16-lane row, which read a
-// lane of the other half whose partial sum equals its own by then; then the
-// 16- and 32-lane halves through __shfl_xor.  Each step adds a value to its
-// partner's in either order, so all lanes end bitwise equal.
-__device__ __forceinline__ double group_sum(double x, int G) {
-    if (G >= 2) x += dpp_f64<0xB1>(x);
-    if (G >= 4) x += dpp_f64<0x4E>(x);
-    if (G >= 8) x += dpp_f64<0x141>(x);
-    if (G >= 16) x += dpp_f64<0x140>(x);
-    if (G >= 32) x += __shfl_xor(x, 16, 64);
-    if (G >= 64) x += __shfl_xor(x, 32, 64);
-    return x;
-}
-__device__ __forceinline__ cplx group_sum(cplx x, int G) { return cplx{group_sum(x.re, G), group_sum(x.im, G)}; }
-__device__ __forceinline__ double wave_sum(double x) { return group_sum(x, 64); }
-__device__ __forceinline__ double wave_max(double x) {
-    x = fmax(x, dpp_f64<0xB1>(x));
-    x = fmax(x, dpp_f64<0x4E>(x));
-    x = fmax(x, dpp_f64<0x141>(x));
-    x = fmax(x, dpp_f64<0x140>(x));
-    x = fmax(x, __shfl_xor(x, 16, 64));
-    return fmax(x, __shfl_xor(x, 32, 64));
-}
-// Ordering of LDS accesses among the lanes of one wavefront: LDS executes a
-// wavefront's instructions in issue order, so a compiler-level fence at
-// wavefront scope is all that a one-wavefront workgroup needs between a
-// write and another lane's read (no wait for outstanding LDS work).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-// x of lane src (src the same in every lane), read from the register file.
-__device__ __forceinline__ double lane_f64(double x, int src) {
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
-    const int lo = __builtin_amdgcn_readlane((int)(unsigned)(b & 0xffffffffull), src);
-    const int hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), src);
-    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
-}
 // Rotation (c, s) with c^2 + s^2 = 1 to working precision that annihilates
 // the off-diagonal of the real 2x2 [[a, g], [g, b]] (g > 0): t = tan(phi) is
 // the root of t^2 + 2 theta t - 1 = 0 of smaller modulus, theta = (b-a)/(2g).
@@ -1333,7 +1207,8 @@ void k_solve_eig_grouped(const SolveArgs* __restrict__ items) {
 }
 
 // --------------------------------------------------------------------------
-// k_solve_trid: the symmetric solve of k_solve_sym by a method with O(m)
+// k_solve_trid_wide: Hermitian windows of more than 128 columns (the others
+// are solved in trid_solve.hip), by a method with O(m)
 // dependent steps instead of O(m) per Jacobi sweep, for large windows:
 //   1. Householder reduction of xtx to a real symmetric tridiagonal T
 //      (Hermitian input: complex reflectors, T still real);
@@ -1789,30 +1664,14 @@ __device__ void solve_trid_body(const SolveArgs& a) {
     sym_tail<S, NT, kAhead<S, LDS>>(a, ld, Z, spare1, spare2, s_sig, s_perm, nv, 0, true, 0);
 }
 
-template <typename S, int NT, bool LDS>
-__global__ __launch_bounds__(NT)
-void k_solve_trid(SolveArgs a) {
-    solve_trid_body<S, NT, LDS>(a);
-}
-
-// A dense push's Gram finalize (1024 threads, as its own kernel) followed by
-// the tridiagonal solve of the window it completes, in one launch: one
-// kernel boundary fewer on the single-push step.  A rejected snapshot leaves
-// the state as it was, and the solve then finds nothing new (skipped), as
-// after the two separate launches.
-template <bool LDS>
 __global__ __launch_bounds__(1024)
-void k_finalize_solve_trid(double* G, const double* partials, int nblk, SolveArgs a) {
-    gram_finalize_body(G, partials, nblk, a.m, a.slots, a.st);
-    __syncthreads();
-    solve_trid_body<double, 1024, LDS>(a);
+void k_solve_trid_wide(SolveArgs a) {
+    solve_trid_body<cplx, 1024, false>(a);
 }
-
-template <typename S, int NT, bool LDS>
-__global__ __launch_bounds__(NT)
-void k_solve_trid_grouped(const SolveArgs* __restrict__ items) {
+__global__ __launch_bounds__(1024)
+void k_solve_trid_wide_grouped(const SolveArgs* __restrict__ items) {
     const SolveArgs a = items[blockIdx.x];
-    solve_trid_body<S, NT, LDS>(a);
+    solve_trid_body<cplx, 1024, false>(a);
 }
 
 }  // namespace
@@ -1835,38 +1694,15 @@ hipError_t launch_solve_sym(const SolveArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <typename S, bool LDS>
-static hipError_t launch_trid_one(const SolveArgs& a, hipStream_t s) {
-    const int n = a.m, nv = a.r < n ? a.r : n;
-    size_t lds = sizeof(double) * 2 * (size_t)n * nv;
-    if (LDS) lds += sizeof(S) * (size_t)n * (n + 1);
-    auto kern = k_solve_trid<S, 1024, LDS>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(1), dim3(1024), lds, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_solve_trid(const SolveArgs& a, hipStream_t s) {
-    if (a.r > kRMax || a.m > kMaxM) return hipErrorInvalidValue;
-    if (a.cplx) return a.m <= 32 ? launch_trid_one<cplx, true>(a, s) : launch_trid_one<cplx, false>(a, s);
-    return a.m <= 64 ? launch_trid_one<double, true>(a, s) : launch_trid_one<double, false>(a, s);
-}
-
-hipError_t launch_finalize_solve_trid(double* G, const double* partials, int nblk, const SolveArgs& a,
-                                      hipStream_t s) {
-    if (a.r > kRMax || a.m > kMaxM || a.cplx) return hipErrorInvalidValue;
-    const int n = a.m, nv = a.r < n ? a.r : n;
-    const bool lds_form = a.m <= 64;
-    size_t lds = sizeof(double) * 2 * (size_t)n * nv;
-    if (lds_form) lds += sizeof(double) * (size_t)n * (n + 1);
-    const void* kern = lds_form ? reinterpret_cast<const void*>(k_finalize_solve_trid<true>)
-                                : reinterpret_cast<const void*>(k_finalize_solve_trid<false>);
+// Hermitian windows of more than 128 columns: one window by value, or n items.
+hipError_t launch_solve_trid_wide(const SolveArgs* one, const SolveArgs* items, int n, hipStream_t s) {
+    const size_t lds = sizeof(double) * 2 * kMaxM * kRMax;
+    const void* kern = one ? reinterpret_cast<const void*>(k_solve_trid_wide)
+                           : reinterpret_cast<const void*>(k_solve_trid_wide_grouped);
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    if (lds_form) hipLaunchKernelGGL(k_finalize_solve_trid<true>, dim3(1), dim3(1024), lds, s, G, partials, nblk, a);
-    else hipLaunchKernelGGL(k_finalize_solve_trid<false>, dim3(1), dim3(1024), lds, s, G, partials, nblk, a);
+    if (one) hipLaunchKernelGGL(k_solve_trid_wide, dim3(1), dim3(1024), lds, s, *one);
+    else hipLaunchKernelGGL(k_solve_trid_wide_grouped, dim3(n), dim3(1024), lds, s, items);
     return hipGetLastError();
 }
 
@@ -1879,54 +1715,6 @@ hipError_t launch_solve_eig(const SolveArgs& a, hipStream_t s) {
 }  // namespace dmd
 
 namespace dmd {
-
-hipError_t launch_trid_grouped(const SolveArgs* items_lds, int n_lds, const SolveArgs* items_glb, int n_glb,
-                               hipStream_t s) {
-    // real windows; items_lds: m <= 64, items_glb: m > 64 (dynamic LDS sized for the largest)
-    if (n_lds > 0) {
-        const size_t lds = sizeof(double) * (2 * 64 * kRMax + 64 * 65);
-        auto kern = k_solve_trid_grouped<double, 1024, true>;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(n_lds), dim3(1024), lds, s, items_lds);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (n_glb > 0) {
-        const size_t lds = sizeof(double) * 2 * kMaxM * kRMax;
-        auto kern = k_solve_trid_grouped<double, 1024, false>;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(n_glb), dim3(1024), lds, s, items_glb);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-hipError_t launch_trid_grouped_cplx(const SolveArgs* items_lds, int n_lds, const SolveArgs* items_glb, int n_glb,
-                                    hipStream_t s) {
-    // Hermitian windows (sparse streams); items_lds: m <= 32, items_glb: m > 32
-    if (n_lds > 0) {
-        const size_t lds = sizeof(double) * 2 * 32 * kRMax + sizeof(cplx) * 32 * 33;
-        auto kern = k_solve_trid_grouped<cplx, 1024, true>;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(n_lds), dim3(1024), lds, s, items_lds);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (n_glb > 0) {
-        const size_t lds = sizeof(double) * 2 * kMaxM * kRMax;
-        auto kern = k_solve_trid_grouped<cplx, 1024, false>;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(n_glb), dim3(1024), lds, s, items_glb);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
 
 hipError_t launch_eig_grouped(const SolveArgs* items, int n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
