@@ -689,7 +689,6 @@ __device__ __forceinline__ void vectors_body(const SolveArgs& a, VecShared<S>& s
         const double lam = sh.lsel[v];
         double best = -1e308;
         int tw = 0;
-#pragma unroll 2
         for (int k = hl; k < n; k += 16) {
             double g = sh.d[k] - lam;
             if (k > 0) g -= M[64 * (k - 1) + v] * sh.e[k - 1];
