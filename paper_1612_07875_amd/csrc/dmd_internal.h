@@ -240,9 +240,11 @@ struct ProjectArgs {
     int buildup;           // partial windows (window_cols): X_sub has window_cols columns
 };
 hipError_t launch_project(const ProjectArgs& a, hipStream_t s);
-// Grouped FP32 projections of many streams in one launch.
+// Grouped FP32 projections of many streams in one launch; lds: the largest
+// project_item_lds of the items.
 hipError_t launch_project_grouped(const ProjectArgs* items, const int* blk_start, int nitems, int total_blocks,
-                                  hipStream_t s);
+                                  size_t lds, hipStream_t s);
+size_t project_item_lds(const ProjectArgs& a);
 int project_item_blocks(int64_t n);
 
 // Modes of every window of a block push in one pass over the ring (FP32 data

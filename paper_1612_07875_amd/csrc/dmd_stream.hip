@@ -1731,9 +1731,10 @@ struct TickLayout {
 // the descriptors that the graph's first node copies from pinned memory.
 struct TickShape {
     int buf, count, nl, ng, nt[3], gtot, np, ptot;
+    size_t plds;
     bool operator==(const TickShape& o) const {
         return buf == o.buf && count == o.count && nl == o.nl && ng == o.ng && nt[0] == o.nt[0] && nt[1] == o.nt[1] &&
-               nt[2] == o.nt[2] && gtot == o.gtot && np == o.np && ptot == o.ptot;
+               nt[2] == o.nt[2] && gtot == o.gtot && np == o.np && ptot == o.ptot && plds == o.plds;
     }
 };
 struct TickGraph {
@@ -1937,6 +1938,7 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
     auto* pa = reinterpret_cast<dmd::ProjectArgs*>(H + b->L.proj);
     int* pblk = reinterpret_cast<int*>(H + b->L.pblk);
     int na = 0, nl = 0, ng = 0, np = 0, gtot = 0, ptot = 0;
+    size_t plds = 0;  // LDS of the grouped projection
     int nt[3] = {0, 0, 0}, nc[3] = {0, 0, 0};  // tridiagonal solves by size class, real and Hermitian
     std::vector<int> own;  // members that run their own Gram and projection kernels
     for (int i = 0; i < count; ++i) {
@@ -1964,6 +1966,7 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
                 fill_project_args(h, pa[np], modes[i], ld_modes[i], true);
                 pblk[np] = ptot;
                 ptot += dmd::project_item_blocks(h->n);
+                plds = std::max(plds, dmd::project_item_lds(pa[np]));
                 ++np;
             }
         } else {
@@ -2052,7 +2055,7 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
         if (e != hipSuccess || !modes) return e;
         return phase("batch_project", [&] {
             hipError_t f = np > 0 ? dmd::launch_project_grouped(reinterpret_cast<const dmd::ProjectArgs*>(D + b->L.proj),
-                                                                reinterpret_cast<const int*>(D + b->L.pblk), np, ptot, q)
+                                                                reinterpret_cast<const int*>(D + b->L.pblk), np, ptot, plds, q)
                                   : hipSuccess;
             for (size_t u = 0; u < own.size() && f == hipSuccess; ++u) f = own_project(q, own[u]);
             return f;
@@ -2062,7 +2065,7 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
     // with kernels of their own pass their frames as launch arguments, so
     // such ticks run eagerly
     if (b->graphs > 0 && own.empty()) {
-        const TickShape shape{buf, count, nl, ng, {nt[0], nt[1], nt[2]}, gtot, np, ptot};
+        const TickShape shape{buf, count, nl, ng, {nt[0], nt[1], nt[2]}, gtot, np, ptot, plds};
         TickGraph* tg = nullptr;
         for (TickGraph& g : b->tick_graphs)
             if (g.shape == shape) tg = &g;

@@ -7,11 +7,11 @@
 // interleaved complex output directly.
 //
 // Dense contraction on the matrix cores: v_mfma_f32_16x16x4f32 (FP32) or
-// v_mfma_f64_16x16x4f64 (FP64).  A wavefront owns 64 rows (four 16-row
-// tiles) and all output columns (up to four 16-column tiles); per step of
-// four window columns it loads its A fragments straight from the ring (each
-// lane one element, 16 consecutive rows per column) and the B fragments from
-// the (L2-resident) coefficient matrix.
+// v_mfma_f64_16x16x4f64 (FP64), transposed: the coefficients are the A operand
+// and the window the B operand, so that a lane ends with the real and
+// imaginary parts of its rows and stores them from its registers.  A
+// wavefront owns 64 rows (four 16-row tiles) and all output columns (up to
+// four 16-column tiles).
 //
 // Fragment layouts of the 16x16x4 instructions (checked on the device):
 //   A: lane l holds A[l % 16][l / 16];  B: lane l holds B[l / 16][l % 16];
@@ -64,29 +64,45 @@ template <> struct Acc<float> {
     static __device__ __forceinline__ v4f mma(float a, float b, v4f c) {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
-    static __device__ __forceinline__ int row(int g, int v) { return 4 * g + v; }
 };
 template <> struct Acc<double> {
     using type = v4d;
     static __device__ __forceinline__ v4d mma(double a, double b, v4d c) {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
-    static __device__ __forceinline__ int row(int g, int v) { return g + 4 * v; }
 };
+
+constexpr int kOLD = 17;  // padded row length of the BF16x3 form's output stage
+constexpr int kStage = kThreads / 64 * 64 * kOLD;
+
+// k-steps (of 4 window columns) whose coefficients a lane reads at once, and
+// the coefficients' LDS for m columns: whole groups of k-steps in fragment
+// order, a lane's 16 bytes side by side.
+template <typename T> constexpr int kStepGroup = 16 / sizeof(T);
+template <typename T> __host__ __device__ inline size_t project_lds(int m, int nt) {
+    const int g = 4 * kStepGroup<T>;
+    return sizeof(T) * (size_t)((m + g - 1) / g * g) * 16 * nt;
+}
 
 // TX: ring element type; T: coefficient, accumulation and output type.
 // NT: number of 16-column output tiles (kcols <= 16 NT).
-// The A and B fragments of the next group of four k-steps are loaded while
-// the current group's MFMAs run; output tiles go through LDS so that every
-// store instruction writes 64 consecutive rows of one output column.
-constexpr int kOLD = 17;  // padded row length of the output stage
-constexpr int kStage = kThreads / 64 * 64 * kOLD;
-
+// Row li of tile rt is row 32 (rt / 2) + 2 li + rt % 2 of the wavefront's 64,
+// so that a lane loads two neighbouring rows at once (128 bytes of a column
+// over 16 lanes; 4-byte loads of one row took twice the instructions) and
+// holds two neighbouring rows of its output columns: 16-byte stores of 256
+// contiguous bytes per complex FP32 column.  Bound by HBM up to about m = 64,
+// r = 20 and by the matrix cores at m = 256, r = 32 (FP32: 225 us at
+// n = 2^20); the loads of the next group of k-steps are in flight during the
+// products of the current one.
 template <typename TX, typename T, int NT>
-__device__ void project_body(const ProjectArgs& a, int blk, T* stage) {
+__device__ __forceinline__ void project_body(const ProjectArgs& a, int blk, T* coef) {
     using AccT = typename Acc<T>::type;
-    constexpr int KG = sizeof(T) == 8 ? 2 : 4;  // k-steps (of 4 columns) per group
-    constexpr int OLD = kOLD;
+    typedef TX x2 __attribute__((ext_vector_type(2)));
+    typedef T tv __attribute__((ext_vector_type(kStepGroup<T>)));
+    typedef T t4 __attribute__((ext_vector_type(4)));
+    typedef T t2 __attribute__((ext_vector_type(2)));
+    constexpr int KS = kStepGroup<T>;             // k-steps per group
+    constexpr bool F64 = sizeof(T) == 8;
     const DevState* st = a.st;
     if (st->solve_status == ST_E_NOT_READY) return;
     if (a.block_only && st->block_rejected) return;
@@ -98,97 +114,131 @@ __device__ void project_body(const ProjectArgs& a, int blk, T* stage) {
     const T* B = reinterpret_cast<const T*>(a.B);
 
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = lane & 15, lk = lane >> 4;
     const int64_t row0 = (int64_t)blk * kRowsPerBlock + wave * kRowsPerWave;
+    const bool live = row0 < a.n;  // (row0 + 63 < ld: the ring's columns are padded to whole 64 rows)
     const int oldest = st->oldest;
-    const TX* ring = reinterpret_cast<const TX*>(a.ring);
+    const TX* ring = reinterpret_cast<const TX*>(a.ring) + (live ? row0 : 0) + 2 * li;
+
+    // window columns lk, 4 + lk, ...: past the window, its last column again
+    // (times a zero coefficient)
+    const int ngroups = (m + 4 * KS - 1) / (4 * KS);
+    x2 xv[KS][2], n1[KS][2], n2[KS][2];
+    auto load_group = [&](x2 (&x)[KS][2], int g) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const int col = min(4 * (g * KS + s) + lk, m - 1);
+            const TX* p = ring + (int64_t)slot_of(oldest, a.first + col, a.slots) * a.ld;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) x[s][h] = __builtin_nontemporal_load(reinterpret_cast<const x2*>(p + 32 * h));
+        }
+    };
+    load_group(xv, 0);
+    load_group(n1, 1);
+    // the coefficients in fragment order: entry (column k, output c) for k-step
+    // s of group g in lane 16 (k % 4) + i, i = the operand row that ends as
+    // output c: D row 4 lk + v (FP32) or lk + 4 v (FP64) holds c = 4 lk + v
+    // (eight loads in flight per thread: one at a time, the 64 KB of m = 256,
+    // r = 32 took a quarter of the workgroup's time)
+    const int total = 4 * KS * ngroups * 16 * NT;
+    for (int base = threadIdx.x; base < total; base += 8 * kThreads) {
+        T v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int idx = base + u * kThreads, k = idx / (16 * NT), c = idx % (16 * NT);
+            const bool in = k < m && c < kcols;
+            const T x = B[in ? (int64_t)k * rowstride + c : 0];
+            v[u] = in ? x : T(0);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int idx = base + u * kThreads, k = idx / (16 * NT), c = idx % (16 * NT);
+            const int ct = c & 15, i = F64 ? 4 * (ct & 3) + (ct >> 2) : ct;
+            if (idx < total) coef[((((k / (4 * KS)) * NT + (c >> 4)) * 64) + 16 * (k & 3) + i) * KS + (k / 4) % KS] = v[u];
+        }
+    }
+    __syncthreads();
+    if (!live) return;
 
     AccT acc[4][NT];
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[rt][nt] = AccT{0, 0, 0, 0};
-
-    bool rin[4];
+    for (int g = 0; g < ngroups; ++g) {
+        load_group(n2, g + 2);  // (past the last group: the last column once more)
+        __builtin_amdgcn_sched_barrier(0);  // (the loads are issued before the products)
+        tv cv[NT];
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt) rin[rt] = row0 + 16 * rt + li < a.n;
-
-    T av[2][KG][4], bv[2][KG][NT];
-    auto load_group = [&](int buf, int k0) {
+        for (int nt = 0; nt < NT; ++nt) cv[nt] = *reinterpret_cast<const tv*>(coef + ((g * NT + nt) * 64 + lane) * KS);
 #pragma unroll
-        for (int g = 0; g < KG; ++g) {
-            const int col = k0 + 4 * g + lk;
-            const bool cin = col < m;
-            const TX* cp = ring + (int64_t)slot_of(oldest, a.first + (cin ? col : 0), a.slots) * a.ld;
-#pragma unroll
-            for (int rt = 0; rt < 4; ++rt)
-                av[buf][g][rt] = (cin && rin[rt]) ? (T)__builtin_nontemporal_load(&cp[row0 + 16 * rt + li]) : T(0);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int c = 16 * nt + li;
-                bv[buf][g][nt] = (cin && c < kcols) ? B[(int64_t)col * rowstride + c] : T(0);
-            }
-        }
-    };
-    auto mma_group = [&](int buf) {
-#pragma unroll
-        for (int g = 0; g < KG; ++g)
+        for (int s = 0; s < KS; ++s)
 #pragma unroll
             for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    acc[rt][nt] = Acc<T>::mma(av[buf][g][rt], bv[buf][g][nt], acc[rt][nt]);
-    };
-    // two groups per iteration so that both register buffers have static indices
-    const int ngroups = (m + 4 * KG - 1) / (4 * KG);
-    load_group(0, 0);
-    for (int gi = 0; gi < ngroups; gi += 2) {
-        if (gi + 1 < ngroups) load_group(1, (gi + 1) * 4 * KG);
-        mma_group(0);
-        if (gi + 1 >= ngroups) break;
-        if (gi + 2 < ngroups) load_group(0, (gi + 2) * 4 * KG);
-        mma_group(1);
+                    acc[rt][nt] = Acc<T>::mma(cv[nt][s], (T)xv[s][rt >> 1][rt & 1], acc[rt][nt]);
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                xv[s][h] = n1[s][h];
+                n1[s][h] = n2[s][h];
+            }
     }
 
     // window columns are read and modes written nontemporally: each is
     // touched once per call, and the solves of the next push, which may run
     // beside this kernel, keep their data cached
     T* out = reinterpret_cast<T*>(a.out);
-    T* sw = stage + wave * 64 * OLD;
-    const int64_t row = row0 + lane;  // the row this lane stores
+    const bool wide = ((uintptr_t)out | (uintptr_t)(sizeof(T) * (a.cplx_out ? 2 : 1) * a.ldo)) % 16 == 0;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-        if (16 * nt >= kcols) break;
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) sw[(16 * rt + Acc<T>::row(lk, v)) * OLD + li] = acc[rt][nt][v];
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (row < a.n) {
+        for (int h = 0; h < 2; ++h) {
+            const int64_t row = row0 + 32 * h + 2 * li;
+            const bool r0 = row < a.n, r1 = row + 1 < a.n;
+            const AccT &p = acc[2 * h][nt], &q = acc[2 * h + 1][nt];  // rows row, row + 1
             if (a.cplx_out) {
 #pragma unroll
-                for (int cc = 0; cc < 16; cc += 2) {
-                    const int c = 16 * nt + cc;
-                    if (c < kcols) {
-                        const int64_t o = 2 * (row + (int64_t)(c >> 1) * a.ldo);
-                        __builtin_nontemporal_store(sw[lane * OLD + cc], &out[o]);
-                        __builtin_nontemporal_store(sw[lane * OLD + cc + 1], &out[o + 1]);
+                for (int v = 0; v < 4; v += 2) {
+                    const int c = 16 * nt + 4 * lk + v;
+                    if (c >= kcols) continue;
+                    T* o = out + 2 * (row + (int64_t)(c >> 1) * a.ldo);
+                    if (wide && r1) {
+                        if constexpr (F64) {
+                            __builtin_nontemporal_store(t2{p[v], p[v + 1]}, reinterpret_cast<t2*>(o));
+                            __builtin_nontemporal_store(t2{q[v], q[v + 1]}, reinterpret_cast<t2*>(o + 2));
+                        } else {
+                            __builtin_nontemporal_store(t4{p[v], p[v + 1], q[v], q[v + 1]}, reinterpret_cast<t4*>(o));
+                        }
+                    } else {
+                        if (r0) {
+                            __builtin_nontemporal_store(p[v], o);
+                            __builtin_nontemporal_store(p[v + 1], o + 1);
+                        }
+                        if (r1) {
+                            __builtin_nontemporal_store(q[v], o + 2);
+                            __builtin_nontemporal_store(q[v + 1], o + 3);
+                        }
                     }
                 }
             } else {
 #pragma unroll
-                for (int cc = 0; cc < 16; ++cc) {
-                    const int c = 16 * nt + cc;
-                    if (c < kcols) out[row + (int64_t)c * a.ldo] = sw[lane * OLD + cc];
+                for (int v = 0; v < 4; ++v) {
+                    const int c = 16 * nt + 4 * lk + v;
+                    if (c >= kcols) continue;
+                    T* o = out + row + (int64_t)c * a.ldo;
+                    if (wide && r1) {
+                        *reinterpret_cast<t2*>(o) = t2{p[v], q[v]};
+                    } else {
+                        if (r0) o[0] = p[v];
+                        if (r1) o[1] = q[v];
+                    }
                 }
             }
         }
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 }
 
@@ -197,7 +247,7 @@ __device__ void project_body(const ProjectArgs& a, int blk, T* stage) {
 // consecutive rows of one coefficient column (B) of the 16x16x32 fragments
 // (A[l%16][8(l/16)+e], B[8(l/16)+e][l%16]; D as the f32 16x16x4 layout).
 template <int NT>
-__device__ void project_body_bf3(const ProjectArgs& a, int blk, float* stage) {
+__device__ __forceinline__ void project_body_bf3(const ProjectArgs& a, int blk, float* stage) {
     constexpr int OLD = kOLD;
     const DevState* st = a.st;
     if (st->solve_status == ST_E_NOT_READY) return;
@@ -295,8 +345,8 @@ __device__ void project_body_bf3(const ProjectArgs& a, int blk, float* stage) {
 template <typename TX, typename T, int NT>
 __global__ __launch_bounds__(kThreads)
 void k_project_mfma(ProjectArgs a) {
-    __shared__ T stage[kStage];
-    project_body<TX, T, NT>(a, blockIdx.x, stage);
+    extern __shared__ double pdyn[];
+    project_body<TX, T, NT>(a, blockIdx.x, reinterpret_cast<T*>(pdyn));
 }
 
 template <int NT>
@@ -308,10 +358,11 @@ void k_project_bf3(ProjectArgs a) {
 
 // Grouped form over many streams (FP32 ring and coefficients; each item in
 // FP32 or BF16x3 by its precision): block b belongs to item i with
-// blk_start[i] <= b < blk_start[i+1].
-template <int NT>
-__global__ __launch_bounds__(kThreads)
+// blk_start[i] <= b < blk_start[i+1].  Each item runs with the column tiles
+// its rank needs.
+__global__ __launch_bounds__(kThreads, 3)
 void k_project_grouped(const ProjectArgs* __restrict__ items, const int* __restrict__ blk_start, int nitems) {
+    extern __shared__ double pdyn[];
     int lo = 0, hi = nitems - 1;
     const int b = blockIdx.x;
     while (lo < hi) {
@@ -320,15 +371,30 @@ void k_project_grouped(const ProjectArgs* __restrict__ items, const int* __restr
         else hi = mid - 1;
     }
     const ProjectArgs a = items[lo];
-    __shared__ float stage[kStage];
-    if (a.precision == 2 /* DMD_PREC_BF16X3 */) project_body_bf3<NT>(a, b - blk_start[lo], stage);
-    else project_body<float, float, NT>(a, b - blk_start[lo], stage);
+    const int blk = b - blk_start[lo];
+    float* lds = reinterpret_cast<float*>(pdyn);
+    const int nt = ((a.cplx_out ? 2 * a.kmax : a.kmax) + 15) / 16;
+    if (a.precision == 2 /* DMD_PREC_BF16X3 */) {
+        project_body_bf3<4>(a, blk, lds);
+        return;
+    }
+    switch (nt) {
+        case 1: project_body<float, float, 1>(a, blk, lds); break;
+        case 2: project_body<float, float, 2>(a, blk, lds); break;
+        case 3: project_body<float, float, 3>(a, blk, lds); break;
+        default: project_body<float, float, 4>(a, blk, lds); break;
+    }
 }
 
 template <typename TX, typename T, int NT>
 hipError_t launch_nt(const ProjectArgs& a, hipStream_t s) {
     const unsigned gx = (unsigned)((a.n + kRowsPerBlock - 1) / kRowsPerBlock);
-    hipLaunchKernelGGL((k_project_mfma<TX, T, NT>), dim3(gx), dim3(kThreads), 0, s, a);
+    const size_t lds = project_lds<T>(a.m, NT);
+    auto kern = k_project_mfma<TX, T, NT>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(gx), dim3(kThreads), lds, s, a);
     return hipGetLastError();
 }
 
@@ -1729,10 +1795,18 @@ hipError_t launch_project_block(const BlockProjectArgs& a, hipStream_t s) {
 
 int project_item_blocks(int64_t n) { return (int)((n + kRowsPerBlock - 1) / kRowsPerBlock); }
 
+// LDS of one item of a grouped launch.
+size_t project_item_lds(const ProjectArgs& a) {
+    if (a.precision == 2 /* DMD_PREC_BF16X3 */) return sizeof(float) * kStage;
+    return project_lds<float>(a.m, ((a.cplx_out ? 2 * a.kmax : a.kmax) + 15) / 16);
+}
+
 hipError_t launch_project_grouped(const ProjectArgs* items, const int* blk_start, int nitems, int total_blocks,
-                                  hipStream_t s) {
-    // four 16-column tiles cover every r <= 32
-    hipLaunchKernelGGL(k_project_grouped<4>, dim3(total_blocks), dim3(kThreads), 0, s, items, blk_start, nitems);
+                                  size_t lds, hipStream_t s) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_project_grouped),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_project_grouped, dim3(total_blocks), dim3(kThreads), lds, s, items, blk_start, nitems);
     return hipGetLastError();
 }
 
