@@ -10,9 +10,9 @@
 //   * A~ = Sigma^-1 V^* (X^* X') V Sigma^-1 from the Gram block xty without
 //     forming U (Eq. Atilde; Algorithm 2; Sec. 3.4);
 //   * POD coefficients V Sigma^-1 (Sec. 2.1, step 2).
-// k_solve_eig (one wavefront):
-//   * A~ W = W Lambda: Householder reduction to Hessenberg form, single-shift
-//     complex QR iteration with Wilkinson shifts and deflation to Schur form
+// k_solve_eig (one workgroup):
+//   * A~ W = W Lambda: Householder reduction to Hessenberg form, QR iteration
+//     (real A~: double shifts; complex: Wilkinson shifts) to the Schur form
 //     A~ = Z T Z^*, eigenvectors of T by back substitution, W = Z Y;
 //   * eigenpairs sorted (|lambda| descending, arg ascending), W's columns
 //     scaled to unit norm with the largest-modulus entry real positive;
@@ -20,6 +20,8 @@
 //     mode argmin |log lambda| (Algorithm 3);
 //   * DMD coefficients C = V Sigma^-1 W for the projection Phi = X' C (Eq. Phi)
 //     and the background coefficients C[:, bg] b_bg lambda_bg^m.
+#include <type_traits>
+
 #include "solve_common.h"
 
 namespace dmd {
@@ -499,40 +501,142 @@ void k_solve_sym_grouped(const SolveArgs* __restrict__ items) {
 }
 
 // --------------------------------------------------------------------------
-// k_solve_eig: one wavefront, A~ (k x k, k <= 32) in LDS
+// k_solve_eig: A~ (k x k, k <= 32) in LDS, 4 wavefronts.  The Hessenberg
+// reduction, the QR iteration and the triangular solves are one wavefront's
+// (chains of dependent steps); products with all eigenvectors are shared.
+//
+// M holds H in rows 0 .. 31 and the accumulated transformation Z in rows
+// 32 .. 63 of the same columns: a transformation from the right is one
+// instruction stream for the 64 lanes (lane = row of either), and H's rows
+// past the active ones are zero there, so no lane needs a mask.  Odd column
+// stride: lanes along a row (lane = column) and along a column hit different
+// banks.
+//
+// Bound by the latency of those chains.  Against one wavefront with H and Z in
+// arrays of their own and b from a pivoted elimination of W Lambda: r = 10 real
+// 117 -> 73 us, r = 20 330 -> 189, r = 32 857 -> 397, r = 24 complex 685 -> 495;
+// 24 windows of a tick 878 -> 462.
 // --------------------------------------------------------------------------
-// Column stride of the k x k (k <= kRMax) matrices in LDS: one more than
-// kRMax, so that a row read across lanes (lane = column) spreads over the
-// LDS banks instead of hitting the same one from every lane.
-constexpr int LDH = kRMax + 1;
+constexpr int LDM = 65;
+constexpr int kEigCols = 40;  // 32, and the (zero) columns that a run of eight may reach past them
+constexpr int kEigThreads = 256;
+constexpr int LDH = kRMax + 1;  // column stride of the eigenvector matrices
 
+template <int I, int N, typename F> __device__ __forceinline__ void each_i(F f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        each_i<I + 1, N>(f);
+    }
+}
+__device__ __forceinline__ double sqr(double a) { return a * a; }
+__device__ __forceinline__ double sqr(cplx a) { return fma(a.im, a.im, a.re * a.re); }
+__device__ __forceinline__ double fmac(double a, double b, double c) { return fma(a, b, c); }
+__device__ __forceinline__ cplx fmac(cplx a, cplx b, cplx c) {
+    return {fma(-a.im, b.im, fma(a.re, b.re, c.re)), fma(a.im, b.re, fma(a.re, b.im, c.im))};
+}
+__device__ __forceinline__ cplx fmac(double a, cplx b, cplx c) { return {fma(a, b.re, c.re), fma(a, b.im, c.im)}; }
+__device__ __forceinline__ double other_half_sum(double x) {  // x of this lane plus x of lane ^ 32
+    return row_fold<32>(x, [](double a, double b) { return a + b; });
+}
+__device__ __forceinline__ cplx other_half_sum(cplx x) { return {other_half_sum(x.re), other_half_sum(x.im)}; }
+// a / b by the reciprocal of |b|^2 where that is in range
+__device__ __forceinline__ cplx div_fast(cplx a, cplx b) {
+    const double b2 = sqr(b);
+    if (b2 > 1e-280 && b2 < 1e280) return rcp_acc(b2) * mul_conj(a, b);
+    return cdiv(a, b);
+}
 
-// Real Schur form of the real upper Hessenberg k x k matrix held in the real
-// parts of H (imaginary parts zero), one wavefront: implicit double-shift
+// Householder reduction of H to upper Hessenberg form, Z accumulating: column
+// c's reflector u (kept unnormalized, in hv) from the left (lane = column, its
+// rows c+1 .. in registers, eight at a time) and from the right (lane = row of
+// H or Z).  Entries past the matrix meet zeros of u.
+template <typename S>
+__device__ __forceinline__ void hessenberg(S* M, S* hv, int k, int lane) {
+    using SC = Scal<S>;
+    for (int c = 0; c + 2 < k; ++c) {
+        const int len = k - c - 1;  // rows c+1 .. k-1
+        const S* col = M + c * LDM + c + 1;
+        const S xl = lane < len ? col[lane < len ? lane : 0] : SC::zero();
+        const S x0 = col[0];
+        const double tail2 = wave_sum(lane >= 1 && lane < len ? sqr(xl) : 0.0);
+        if (__builtin_amdgcn_readfirstlane(tail2 == 0.0)) continue;
+        const double ax0 = SC::absv(x0), alpha = sqrt(ax0 * ax0 + tail2);
+        const S ph = SC::phase(x0);
+        wave_sync();
+        if (lane < 32) hv[lane] = lane == 0 ? x0 + ph * alpha : xl;
+        wave_sync();
+        const double tau = 1.0 / (alpha * (alpha + ax0));
+        S r[32];
+        auto reflect = [&](S* p, int stride, bool left) {
+            S w0 = SC::zero(), w1 = SC::zero();
+            each_i<0, 4>([&](auto ch) {
+                if (8 * ch() < len)
+                    each_i<0, 8>([&](auto u) {
+                        constexpr int i = 8 * ch() + u();
+                        r[i] = p[i * stride];
+                        const S v = left ? SC::cj(hv[i]) : hv[i];
+                        if constexpr (i % 2) w1 = fmac(r[i], v, w1);
+                        else w0 = fmac(r[i], v, w0);
+                    });
+            });
+            const S w = (w0 + w1) * -tau;
+            each_i<0, 4>([&](auto ch) {
+                if (8 * ch() < len)
+                    each_i<0, 8>([&](auto u) {
+                        constexpr int i = 8 * ch() + u();
+                        p[i * stride] = fmac(left ? hv[i] : SC::cj(hv[i]), w, r[i]);
+                    });
+            });
+        };
+        reflect(M + (lane & 31) * LDM + c + 1, 1, true);  // (both halves of the wavefront alike)
+        wave_sync();
+        reflect(M + (c + 1) * LDM + lane, LDM, false);
+        wave_sync();
+        if (lane < len) M[c * LDM + c + 1 + lane] = lane == 0 ? ph * -alpha : SC::zero();
+        wave_sync();
+    }
+}
+
+// Deflation: the largest l in [1, hi] with a negligible subdiagonal entry
+// (set to zero), else 0.
+template <typename S>
+__device__ __forceinline__ int deflate(S* M, int hi, int lane, double hmax) {
+    using SC = Scal<S>;
+    bool small = false;
+    if (lane >= 1 && lane <= hi) {
+        const double sub = SC::absv(M[(lane - 1) * LDM + lane]);
+        double scale = SC::absv(M[lane * LDM + lane]) + SC::absv(M[(lane - 1) * LDM + lane - 1]);
+        if (scale == 0.0) scale = hmax;
+        small = sub <= kEps * scale;
+    }
+    const unsigned long long mask = __ballot(small);
+    const int l = mask ? 63 - __clzll(mask) : 0;
+    wave_sync();
+    if (l > 0 && lane == 0) M[(l - 1) * LDM + l] = SC::zero();
+    wave_sync();
+    return l;
+}
+
+// Real Schur form of the real upper Hessenberg H: implicit double-shift
 // (Francis) QR -- each sweep chases a 3 x 3 Householder bulge started from
 // the first column of (H - mu1)(H - mu2), mu1,2 the eigenvalues of the
 // trailing 2 x 2 block (an exceptional pair every 10th sweep), so that a
-// complex-conjugate pair converges together in real arithmetic; Z (complex
-// storage, real values) accumulates the transformations.  The 2 x 2 blocks
-// left on the diagonal are then triangularized by one complex rotation each,
-// so that H becomes the complex upper triangular T of the complex Schur form.
-__device__ __forceinline__ void real_schur(cplx* H, cplx* Z, int k, int lane, int max_iter, double hmax, int& total, bool& failed) {
-    auto h = [&](int i, int j) -> double& { return H[i + j * LDH].re; };
+// complex-conjugate pair converges together in real arithmetic.
+//
+// A step is one chain: the reflector from (x, y, z) (in registers: u =
+// (x + sign(x) s, y, z), s = ||(x, y, z)||, tau = 1 / (s (s + |x|)), by the
+// hardware estimates plus Newton steps), the three rows (lane = column), LDS,
+// the three columns (lane = row of H or Z), and the next (x, y, z) from the
+// lanes that hold them.  About 80 instructions, 450 cycles measured; with the
+// rows of Z apart from H's, masked writes and 2 / v^T v summed up it took
+// 1000 to 1200.
+__device__ __forceinline__ void real_schur(double* M, int k, int lane, int max_iter, double hmax, int& total,
+                                           bool& failed) {
+    auto h = [&](int i, int j) -> double& { return M[j * LDM + i]; };
+    const int j = lane & 31;
     int nn = k - 1, its = 0;
     while (nn >= 0) {
-        // deflation: largest l in [1, nn] with a negligible subdiagonal
-        bool small = false;
-        if (lane >= 1 && lane <= nn) {
-            const double sub = fabs(h(lane, lane - 1));
-            double scale = fabs(h(lane, lane)) + fabs(h(lane - 1, lane - 1));
-            if (scale == 0.0) scale = hmax;
-            small = sub <= kEps * scale;
-        }
-        const unsigned long long mask = __ballot(small);
-        const int l = mask ? 63 - __clzll(mask) : 0;
-        wave_sync();
-        if (l > 0 && lane == 0) h(l, l - 1) = 0.0;
-        wave_sync();
+        const int l = deflate(M, nn, lane, hmax);
         if (l >= nn - 1) {  // a 1 x 1 or 2 x 2 block splits off
             nn = l - 1;
             its = 0;
@@ -558,248 +662,60 @@ __device__ __forceinline__ void real_schur(cplx* H, cplx* Z, int k, int lane, in
                 t = a11 * a22 - a12 * a21;
             }
         }
-        // (x, y, z): the first column of (H - mu1)(H - mu2) to start the
-        // sweep, then the bulge below the subdiagonal of column kk-1; the
-        // latter were just written by the lanes that updated column kk-1,
-        // and are read from their registers (the LDS copy only when that
-        // step applied no reflector)
         double x, y, z;
         {
             const double h00 = h(l, l), h10 = h(l + 1, l);
             x = h00 * h00 + h(l, l + 1) * h10 - s * h00 + t;
             y = h10 * (h00 + h(l + 1, l + 1) - s);
             z = h10 * h(l + 2, l + 1);
+            // (products of entries: scaled, so that their squares stay in range)
+            const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(x), fmax(fabs(y), fabs(z))));
+            x = ldexp(x, e);
+            y = ldexp(y, e);
+            z = ldexp(z, e);
         }
-        // One bulge step is straight-line code: every lane reads its column
-        // (rows kk .. kk+2) and its row of Z (columns kk .. kk+2) before the
-        // reflector is known, and lanes outside a range write to a sink
-        // entry past the matrix instead of branching, so that the updates
-        // of H's rows and of Z interleave.
-        const int lc = lane < LDH ? lane : LDH - 1;  // this lane's column / row, clamped
-        const int sink = LDH * LDH + lane;
         for (int kk = l; kk < nn; ++kk) {
-            const bool three = kk + 2 <= nn;
-            const double r0 = h(kk, lc), r1 = h(kk + 1, lc), r2 = h(kk + 2, lc);
-            const double zc0 = Z[lc + kk * LDH].re, zc1 = Z[lc + (kk + 1) * LDH].re, zc2 = Z[lc + (kk + 2) * LDH].re;
-            // (the bulge chase is a chain of dependent FP64 steps: the norm and
-            // 2 / v^T v come from the hardware estimates plus Newton steps,
-            // shorter chains than the correctly rounded square root and division)
-            const double s2 = x * x + y * y + z * z;
-            const double nrm = s2 > 0.0 ? s2 * rsqrt_acc(s2) : 0.0;
-            // reflector P = I - tau v v^T, v = (x - alpha, y, z), P (x, y, z) = (alpha, 0, 0)
-            // (z = 0 exactly when the step has two rows)
-            const double alpha = x > 0.0 ? -nrm : nrm;
-            const double v0 = x - alpha;
-            const double vtv = v0 * v0 + y * y + z * z;
-            const double tau = vtv > 0.0 ? 2.0 * rcp_acc(vtv) : 0.0;
-            double nc0 = 0.0;  // this lane's new H[lane][kk]
-            if (tau != 0.0) {
-                // rows kk .. kk+2 over columns jlo .. k-1 (lane = column); the
-                // entries below the subdiagonal of column kk-1 become zero
-                const int jlo = kk > l ? kk - 1 : l;
-                const bool rok = lane >= jlo && lane < k;
-                const double f = tau * (v0 * r0 + y * r1 + z * r2);
-                const bool below = kk > l && lane == kk - 1;
-                H[rok ? kk + lc * LDH : sink].re = r0 - f * v0;
-                H[rok ? kk + 1 + lc * LDH : sink].re = below ? 0.0 : r1 - f * y;
-                H[rok && three ? kk + 2 + lc * LDH : sink].re = below ? 0.0 : r2 - f * z;
-                // Z over all rows (lane = row)
-                const bool zok = lane < k;
-                const double fz = tau * (zc0 * v0 + zc1 * y + zc2 * z);
-                Z[zok ? lc + kk * LDH : sink].re = zc0 - fz * v0;
-                Z[zok ? lc + (kk + 1) * LDH : sink].re = zc1 - fz * y;
-                Z[zok && three ? lc + (kk + 2) * LDH : sink].re = zc2 - fz * z;
-                wave_sync();
-                // columns kk .. kk+2 over rows 0 .. min(kk+3, nn) (lane = row)
-                const int ihi = kk + 3 < nn ? kk + 3 : nn;
-                const bool cok = lane <= ihi;
-                const double c0 = h(lc, kk), c1 = h(lc, kk + 1), c2 = h(lc, kk + 2);
-                const double fc = tau * (c0 * v0 + c1 * y + c2 * z);
-                nc0 = c0 - fc * v0;
-                H[cok ? lc + kk * LDH : sink].re = nc0;
-                H[cok ? lc + (kk + 1) * LDH : sink].re = c1 - fc * y;
-                H[cok && three ? lc + (kk + 2) * LDH : sink].re = c2 - fc * z;
-            }
+            double* row = M + j * LDM + kk;     // rows kk .. kk+2 of column j
+            double* col = M + kk * LDM + lane;  // columns kk .. kk+2 of row `lane`
+            const double r0 = row[0], r1 = row[1], r2 = row[2];
+            const double s2 = fma(x, x, fma(y, y, z * z));
+            const bool none = !(s2 > 1e-300);   // (nothing to annihilate: z and y are zero, or vanish beside H)
+            const double inv = rsqrt_acc(s2);
+            const double nrm = s2 * inv, ax = fabs(x);
+            const double u0 = none ? 0.0 : x + copysign(nrm, x);
+            const double tau = none ? 0.0 : inv * rcp_acc(nrm + ax);
+            const double f = tau * fma(u0, r0, fma(y, r1, z * r2));
+            // the entries below the subdiagonal of column kk-1 become zero
+            const bool below = kk > l && j == kk - 1;
+            const double n0 = fma(-f, u0, r0), n1 = fma(-f, y, r1), n2 = fma(-f, z, r2);
+            row[0] = n0;
+            row[1] = below && !none ? 0.0 : n1;
+            row[2] = below && !none && kk + 2 <= nn ? 0.0 : n2;
             wave_sync();
-            if (kk + 1 < nn) {
-                // rows kk+1 .. kk+3 of column kk (rows 0 .. kk+3 were updated above)
-                const bool z3 = kk + 3 <= nn;
-                if (tau != 0.0) {
-                    x = lane_f64(nc0, kk + 1);
-                    y = lane_f64(nc0, kk + 2);
-                    z = z3 ? lane_f64(nc0, kk + 3) : 0.0;
-                } else {
-                    x = h(kk + 1, kk);
-                    y = h(kk + 2, kk);
-                    z = z3 ? h(kk + 3, kk) : 0.0;
-                }
-            }
+            const double c0 = col[0], c1 = col[LDM], c2 = col[2 * LDM];
+            const double g = tau * fma(u0, c0, fma(y, c1, z * c2));
+            const double d0 = fma(-g, u0, c0);
+            col[0] = d0;
+            col[LDM] = fma(-g, y, c1);
+            col[2 * LDM] = fma(-g, z, c2);
+            wave_sync();
+            // rows kk+1 .. kk+3 of column kk (z = 0 exactly when the next step has two rows)
+            x = lane_f64(d0, kk + 1);
+            y = lane_f64(d0, kk + 2);
+            z = kk + 3 <= nn ? lane_f64(d0, kk + 3) : 0.0;
         }
-    }
-    wave_sync();
-    // triangularize each 2 x 2 diagonal block [[a, b], [c, d]], c != 0: with
-    // u = (lambda_1 - d, c) / ||.||, lambda_1 an eigenvalue of the block, the
-    // rotation G = [[u0, -conj(u1)], [u1, conj(u0)]] gives G^* B G = [[lambda_1, .], [0, lambda_2]]
-    for (int i = 0; i + 1 < k; ++i) {
-        const double c = h(i + 1, i);
-        if (c == 0.0) continue;
-        const double a = h(i, i), b = h(i, i + 1), d = h(i + 1, i + 1);
-        const double half = 0.5 * (a - d), disc = half * half + b * c;
-        cplx l1;
-        if (disc >= 0.0) l1 = mkc(0.5 * (a + d) + copysign(sqrt(disc), half));
-        else l1 = cplx{0.5 * (a + d), sqrt(-disc)};
-        cplx u0 = l1 - mkc(d), u1 = mkc(c);
-        const double nu = sqrt(abs2(u0) + abs2(u1));
-        u0 = (1.0 / nu) * u0;
-        u1 = (1.0 / nu) * u1;
-        wave_sync();
-        {
-            const int j = lane;  // rows i, i+1 over columns i .. k-1
-            if (j >= i && j < k) {
-                const cplx r0 = H[i + j * LDH], r1 = H[(i + 1) + j * LDH];
-                H[i + j * LDH] = conj_mul(u0, r0) + conj_mul(u1, r1);
-                H[(i + 1) + j * LDH] = u0 * r1 - u1 * r0;
-            }
-        }
-        wave_sync();
-        {
-            const int r = lane;  // columns i, i+1 over rows 0 .. i+1; Z over all rows
-            if (r <= i + 1) {
-                const cplx c0 = H[r + i * LDH], c1 = H[r + (i + 1) * LDH];
-                H[r + i * LDH] = c0 * u0 + c1 * u1;
-                H[r + (i + 1) * LDH] = mul_conj(c1, u0) - mul_conj(c0, u1);
-            }
-            if (r < k) {
-                const cplx c0 = Z[r + i * LDH], c1 = Z[r + (i + 1) * LDH];
-                Z[r + i * LDH] = c0 * u0 + c1 * u1;
-                Z[r + (i + 1) * LDH] = mul_conj(c1, u0) - mul_conj(c0, u1);
-            }
-        }
-        wave_sync();
-        if (lane == 0) H[(i + 1) + i * LDH] = mkc(0.0);
-        wave_sync();
-        ++i;  // the next row belongs to this block
     }
 }
 
-__device__ __forceinline__ void solve_eig_body(const SolveArgs& a) {
-    const int lane = threadIdx.x;
-    DevState* st = a.st;
-    const int status0 = st->solve_status;
-    const int k = st->r_eff;
-    const int m = window_cols(a.m, a.buildup, st);  // columns of X
-    const int ldv = a.m;                            // leading dimension of V
-    if (st->skipped) {
-        publish(a);
-        return;
-    }
-    if (status0 == ST_E_NOT_READY || k == 0) {
-        if (lane == 0 && status0 != ST_E_NOT_READY) st->solves += 1;
-        publish(a);
-        return;
-    }
-
-    __shared__ cplx H[LDH * LDH + 64];  // (64 sink entries past the matrix)
-    __shared__ cplx Z[LDH * LDH + 64];
-    __shared__ cplx Y[LDH * LDH];
-    __shared__ cplx hv[LDH];
-    __shared__ double s_sig[kRMax];
-    __shared__ int s_rank[kRMax];
-
-    for (int idx = lane; idx < LDH * LDH; idx += 64) {
-        const int i = idx % LDH, j = idx / LDH;
-        cplx h = mkc(0.0);
-        if (i < k && j < k) {
-            if (a.cplx) h = cplx{a.At[2 * (i + j * k)], a.At[2 * (i + j * k) + 1]};
-            else h = mkc(a.At[i + j * k]);
-        }
-        H[idx] = h;
-        Z[idx] = mkc(i == j ? 1.0 : 0.0);
-        Y[idx] = mkc(0.0);
-    }
-    if (lane < k) s_sig[lane] = a.sigma[lane];
-    wave_sync();
-
-    // ---- Householder reduction to upper Hessenberg form, Z accumulates
-    for (int c = 0; c + 2 < k; ++c) {
-        const int len = k - c - 1;  // rows c+1 .. k-1
-        double tail2 = 0.0;
-        if (lane >= 1 && lane < len) tail2 = abs2(H[(c + 1 + lane) + c * LDH]);
-        tail2 = wave_sum(tail2);
-        const cplx x0 = H[(c + 1) + c * LDH];
-        const double ax0 = cabs(x0);
-        const double alpha = sqrt(ax0 * ax0 + tail2);
-        if (tail2 == 0.0) {
-            wave_sync();
-            continue;
-        }
-        const cplx ph = ax0 > 0.0 ? cplx{x0.re / ax0, x0.im / ax0} : mkc(1.0);
-        // v = x + ph*alpha e1 ; v^* v = 2 alpha (alpha + |x0|) ; P = I - tau v v^*
-        if (lane < len) hv[lane] = (lane == 0) ? x0 + ph * alpha : H[(c + 1 + lane) + c * LDH];
-        wave_sync();
-        const double tau = 1.0 / (alpha * (alpha + ax0));
-        // left: rows c+1.., columns c..k-1 (lane = column)
-        {
-            const int j = lane;
-            if (j >= c && j < k) {
-                cplx w = mkc(0.0);
-                for (int i = 0; i < len; ++i) w = w + conj_mul(hv[i], H[(c + 1 + i) + j * LDH]);
-                w = tau * w;
-                for (int i = 0; i < len; ++i) H[(c + 1 + i) + j * LDH] = H[(c + 1 + i) + j * LDH] - hv[i] * w;
-            }
-        }
-        wave_sync();
-        // right: all rows, columns c+1.. (lane = row); also Z
-        {
-            const int i = lane;
-            if (i < k) {
-                cplx w = mkc(0.0), wz = mkc(0.0);
-                for (int j = 0; j < len; ++j) {
-                    w = w + H[i + (c + 1 + j) * LDH] * hv[j];
-                    wz = wz + Z[i + (c + 1 + j) * LDH] * hv[j];
-                }
-                w = tau * w;
-                wz = tau * wz;
-                for (int j = 0; j < len; ++j) {
-                    H[i + (c + 1 + j) * LDH] = H[i + (c + 1 + j) * LDH] - mul_conj(w, hv[j]);
-                    Z[i + (c + 1 + j) * LDH] = Z[i + (c + 1 + j) * LDH] - mul_conj(wz, hv[j]);
-                }
-            }
-        }
-        wave_sync();
-        if (lane < len) H[(c + 1 + lane) + c * LDH] = (lane == 0) ? -(ph * alpha) : mkc(0.0);
-        wave_sync();
-    }
-
-    // ---- Schur form T = Z^* A~ Z (full T and Z): real A~ by the implicit
-    // double-shift QR, each 2 x 2 block then triangularized by one complex
-    // rotation; complex A~ by the single-shift complex QR
-    double hmax = 0.0;
-    for (int idx = lane; idx < k * k; idx += 64) hmax = fmax(hmax, cabs(H[(idx % k) + (idx / k) * LDH]));
-    hmax = wave_max(hmax);
-    const double smallnum = (hmax > 0.0 ? hmax : 1.0) * kEps;
-
-    int total = 0;
-    bool failed = false;
-    const int max_iter = a.max_qr_iter;
-    if (!a.cplx) {
-        real_schur(H, Z, k, lane, max_iter, hmax, total, failed);
-    } else {
+// Complex Schur form of the complex upper Hessenberg H: single-shift QR with
+// Wilkinson shifts, one rotation per step (as the real sweep).
+__device__ __forceinline__ void complex_schur(cplx* M, int k, int lane, int max_iter, double hmax, int& total,
+                                              bool& failed) {
+    auto h = [&](int i, int j) -> cplx& { return M[j * LDM + i]; };
+    const int j = lane & 31;
     int hi = k - 1, iter = 0;
     while (hi > 0) {
-        // deflation: largest l in [1, hi] with a negligible subdiagonal
-        bool small = false;
-        if (lane >= 1 && lane <= hi) {
-            const double sub = cabs(H[lane + (lane - 1) * LDH]);
-            double scale = cabs(H[lane + lane * LDH]) + cabs(H[(lane - 1) + (lane - 1) * LDH]);
-            if (scale == 0.0) scale = hmax;
-            small = sub <= kEps * scale;
-        }
-        const unsigned long long mask = __ballot(small);
-        const int l = mask ? 63 - __clzll(mask) : 0;
-        wave_sync();
-        if (l > 0 && lane == 0) H[l + (l - 1) * LDH] = mkc(0.0);
-        wave_sync();
+        const int l = deflate(M, hi, lane, hmax);
         if (l == hi) {
             --hi;
             iter = 0;
@@ -813,8 +729,7 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a) {
         ++total;
         // Wilkinson shift: eigenvalue of the trailing 2x2 closer to H[hi][hi];
         // every 10th iteration an exceptional shift
-        const cplx ta = H[(hi - 1) + (hi - 1) * LDH], tb = H[(hi - 1) + hi * LDH];
-        const cplx tc = H[hi + (hi - 1) * LDH], td = H[hi + hi * LDH];
+        const cplx ta = h(hi - 1, hi - 1), tb = h(hi - 1, hi), tc = h(hi, hi - 1), td = h(hi, hi);
         cplx mu;
         if (iter % 10 == 0) {
             mu = td + mkc(0.75 * cabs(tc));
@@ -825,267 +740,375 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a) {
             // (a+d)/2 +- disc == d + (a-d)/2 +- disc
             mu = (cabs(mu1 - td) <= cabs(mu2 - td)) ? mu1 : mu2;
         }
-        // (x, y): the shifted first column to start the sweep, then the
-        // bulge below the subdiagonal of column kk-1, read from the registers
-        // of the lanes that just updated that column
-        cplx x = H[l + l * LDH] - mu, y = H[(l + 1) + l * LDH];
-        // straight-line steps as in the real sweep: loads first, lanes
-        // outside a range write to a sink entry past the matrix
-        const int lc = lane < LDH ? lane : LDH - 1;
-        const int sink = LDH * LDH + lane;
+        cplx x = h(l, l) - mu, y = h(l + 1, l);
         for (int kk = l; kk < hi; ++kk) {
-            const cplx ru = H[kk + lc * LDH], rv = H[(kk + 1) + lc * LDH];
-            const cplx zu = Z[lc + kk * LDH], zv = Z[lc + (kk + 1) * LDH];
+            cplx* row = M + j * LDM + kk;
+            cplx* col = M + kk * LDM + lane;
+            const cplx ru = row[0], rv = row[1];
             // G = [[c, s], [-conj(s), c]] with G [x; y] = [rho; 0]:
             // c = |x| / r, s = (x / |x|) conj(y) / r, r^2 = |x|^2 + |y|^2
             double c;
             cplx s;
             const double x2 = abs2(x), y2 = abs2(y);
-            if (y2 == 0.0) {
+            if (x2 > 1e-250 && y2 > 1e-250 && x2 < 1e250 && y2 < 1e250) {
+                const double rx = rsqrt_acc(x2), rr = rsqrt_acc(x2 + y2);
+                c = x2 * rx * rr;
+                s = (rx * rr) * mul_conj(x, y);
+            } else if (y2 == 0.0) {
                 c = 1.0;
                 s = mkc(0.0);
             } else if (x2 == 0.0) {
                 c = 0.0;
                 s = mkc(1.0);
-            } else if (x2 > 1e-250 && y2 > 1e-250 && x2 < 1e250 && y2 < 1e250) {
-                const double rx = rsqrt_acc(x2), rr = rsqrt_acc(x2 + y2);
-                c = x2 * rx * rr;
-                s = (rx * rr) * mul_conj(x, y);
             } else {
                 const double ax = cabs(x), rr = hypot(ax, cabs(y));
                 c = ax / rr;
                 s = (1.0 / rr) * mul_conj(cplx{x.re / ax, x.im / ax}, y);
             }
-            // rows kk, kk+1 over columns jlo .. k-1 (lane = column); the entry
-            // below the subdiagonal of column kk-1 becomes zero.  Z over all
-            // rows (lane = row).
-            {
-                const int jlo = kk > l ? kk - 1 : l;
-                const bool rok = lane >= jlo && lane < k;
-                const bool below = kk > l && lane == kk - 1;
-                H[rok ? kk + lc * LDH : sink] = c * ru + s * rv;
-                H[rok ? (kk + 1) + lc * LDH : sink] = below ? mkc(0.0) : c * rv - conj_mul(s, ru);
-                const bool zok = lane < k;
-                Z[zok ? lc + kk * LDH : sink] = c * zu + mul_conj(zv, s);
-                Z[zok ? lc + (kk + 1) * LDH : sink] = c * zv - zu * s;
-            }
+            const bool below = kk > l && j == kk - 1;
+            row[0] = c * ru + s * rv;
+            row[1] = below ? mkc(0.0) : c * rv - conj_mul(s, ru);
             wave_sync();
-            // columns kk, kk+1 over rows 0 .. min(kk+2, hi) (lane = row)
-            cplx nc;  // this lane's new H[lane][kk]
-            {
-                const int ihi = kk + 2 < hi ? kk + 2 : hi;
-                const bool cok = lane <= ihi;
-                const cplx u = H[lc + kk * LDH], v = H[lc + (kk + 1) * LDH];
-                nc = c * u + mul_conj(v, s);
-                H[cok ? lc + kk * LDH : sink] = nc;
-                H[cok ? lc + (kk + 1) * LDH : sink] = c * v - u * s;
-            }
+            const cplx u = col[0], v = col[LDM];
+            const cplx nc = c * u + mul_conj(v, s);
+            col[0] = nc;
+            col[LDM] = c * v - u * s;
             wave_sync();
-            if (kk + 1 < hi) {  // rows kk+1, kk+2 of column kk (both updated above)
-                x = cplx{lane_f64(nc.re, kk + 1), lane_f64(nc.im, kk + 1)};
-                y = cplx{lane_f64(nc.re, kk + 2), lane_f64(nc.im, kk + 2)};
-            }
+            // rows kk+1, kk+2 of column kk (not used past the last step)
+            x = cplx{lane_f64(nc.re, kk + 1), lane_f64(nc.im, kk + 1)};
+            y = cplx{lane_f64(nc.re, kk + 2), lane_f64(nc.im, kk + 2)};
         }
     }
-    }
-    wave_sync();
+}
 
-    // ---- eigenvectors of the triangular T: (T - t_qq) y = 0, y_q = 1 (lane q)
-    {
-        const int q = lane;
+// Triangularizes each 2 x 2 diagonal block [[a, b], [c, d]], c != 0, of a real
+// Schur form held as complex values: with u = (lambda_1 - d, c) / ||.||,
+// lambda_1 an eigenvalue of the block, the rotation G = [[u0, -conj(u1)],
+// [u1, conj(u0)]] gives G^* B G = [[lambda_1, .], [0, lambda_2]].
+__device__ __forceinline__ void split_blocks(cplx* M, int k, int lane) {
+    const int j = lane & 31;
+    for (int i = 0; i + 1 < k; ++i) {
+        const double c = M[i * LDM + i + 1].re;
+        if (__builtin_amdgcn_readfirstlane(c == 0.0)) continue;
+        const double a = M[i * LDM + i].re, b = M[(i + 1) * LDM + i].re, d = M[(i + 1) * LDM + i + 1].re;
+        const double half = 0.5 * (a - d), disc = half * half + b * c;
+        cplx l1;
+        if (disc >= 0.0) l1 = mkc(0.5 * (a + d) + copysign(sqrt(disc), half));
+        else l1 = cplx{0.5 * (a + d), sqrt(-disc)};
+        cplx u0 = l1 - mkc(d), u1 = mkc(c);
+        const double nu = 1.0 / sqrt(abs2(u0) + abs2(u1));
+        u0 = nu * u0;
+        u1 = nu * u1;
+        wave_sync();
+        {
+            cplx* row = M + j * LDM + i;  // rows i, i+1 (zero before column i)
+            const cplx r0 = row[0], r1 = row[1];
+            row[0] = conj_mul(u0, r0) + conj_mul(u1, r1);
+            row[1] = u0 * r1 - u1 * r0;
+        }
+        wave_sync();
+        {
+            cplx* col = M + i * LDM + lane;  // columns i, i+1 (H zero past row i+1)
+            const cplx c0 = col[0], c1 = col[LDM];
+            col[0] = c0 * u0 + c1 * u1;
+            col[LDM] = mul_conj(c1, u0) - mul_conj(c0, u1);
+        }
+        wave_sync();
+        if (lane == 0) M[i * LDM + i + 1] = mkc(0.0);
+        wave_sync();
+        ++i;  // the next row belongs to this block
+    }
+}
+
+// LDS of the eig solve.
+struct EigShared {
+    cplx M[LDM * kEigCols];                  // H over Z, complex
+    union {
+        double R[LDM * kEigCols];            // real A~: H over Z until the real Schur form
+        cplx Y[LDH * LDH];                   // then the eigenvectors of T, then W in sorted order
+    };
+    union {
+        double hvr[40];
+        cplx hv[40];
+    };
+    cplx lam[kRMax], ls[kRMax];              // eigenvalues: Schur order, sorted
+    cplx x[kRMax];                           // expansion of alpha_1 in the unscaled eigenvectors
+    double mod[kRMax], arg[kRMax], sig[kRMax];
+    cplx fbg;
+    int bg, total, failed;
+};
+
+__device__ __forceinline__ void solve_eig_body(const SolveArgs& a, EigShared& sh) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    DevState* st = a.st;
+    const int status0 = st->solve_status;
+    const int k = st->r_eff;
+    const int m = window_cols(a.m, a.buildup, st);  // columns of X
+    const int ldv = a.m;                            // leading dimension of V
+    if (st->skipped) {
+        publish(a);
+        return;
+    }
+    if (status0 == ST_E_NOT_READY || k == 0) {
+        if (tid == 0 && status0 != ST_E_NOT_READY) st->solves += 1;
+        publish(a);
+        return;
+    }
+    // H = A~, Z = I (columns and rows past k zero)
+    if (a.cplx) {
+        for (int idx = tid; idx < LDM * kEigCols; idx += kEigThreads) {
+            const int i = idx % LDM, jj = idx / LDM;
+            const bool in = i < k && jj < k;
+            const int64_t o = in ? 2 * (i + jj * k) : 0;
+            const double re = a.At[o], im = a.At[o + 1];
+            sh.M[idx] = in ? cplx{re, im} : mkc(i == jj + 32 && jj < 32 ? 1.0 : 0.0);
+        }
+    } else {
+        for (int idx = tid; idx < LDM * kEigCols; idx += kEigThreads) {
+            const int i = idx % LDM, jj = idx / LDM;
+            const bool in = i < k && jj < k;
+            const double v = a.At[in ? i + jj * k : 0];
+            sh.R[idx] = in ? v : i == jj + 32 && jj < 32 ? 1.0 : 0.0;
+        }
+    }
+    if (tid < kRMax) sh.sig[tid] = tid < k ? a.sigma[tid] : 1.0;
+    __syncthreads();
+    if (wave == 0) {
+        int total = 0;
+        bool failed = false;
+        double hmax = 0.0;
+        if (a.cplx) {
+            hessenberg<cplx>(sh.M, sh.hv, k, lane);
+            for (int idx = lane; idx < k * k; idx += 64) hmax = fmax(hmax, cabs(sh.M[(idx / k) * LDM + idx % k]));
+            hmax = wave_max(hmax);
+            complex_schur(sh.M, k, lane, a.max_qr_iter, hmax, total, failed);
+            wave_sync();
+        } else {
+            hessenberg<double>(sh.R, sh.hvr, k, lane);
+            for (int idx = lane; idx < k * k; idx += 64) hmax = fmax(hmax, fabs(sh.R[(idx / k) * LDM + idx % k]));
+            hmax = wave_max(hmax);
+            real_schur(sh.R, k, lane, a.max_qr_iter, hmax, total, failed);
+            wave_sync();
+            for (int jj = 0; jj < kEigCols; ++jj) sh.M[jj * LDM + lane] = mkc(sh.R[jj * LDM + lane]);
+            wave_sync();
+            split_blocks(sh.M, k, lane);
+        }
+        const double smallnum = (hmax > 0.0 ? hmax : 1.0) * kEps;
+        // ---- eigenvectors of the triangular T: (T - t_qq) y = 0, y_q = 1 (lane q)
+        const int q = lane & 31;
+        const cplx lq = sh.M[q * LDM + q];
+        cplx* Yq = sh.Y + q * LDH;
+        if (lane < 32)
+            for (int i = 0; i < LDH; ++i) Yq[i] = mkc(i == q ? 1.0 : 0.0);
+        if (lane < k) sh.lam[lane] = lq;
+        wave_sync();
+        for (int i = k - 2; i >= 0; --i) {
+            cplx a0 = mkc(0.0), a1 = mkc(0.0);
+            for (int j0 = i + 1; j0 < k; j0 += 4) {  // (y_j = 0 past q; T's columns past k are zero)
+                cplx tt[4], yy[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int jj = j0 + u < k ? j0 + u : k - 1;
+                    tt[u] = sh.M[(j0 + u) * LDM + i];
+                    yy[u] = Yq[jj];
+                }
+                a0 = fmac(tt[0], yy[0], a0);
+                a1 = fmac(tt[1], yy[1], a1);
+                a0 = fmac(tt[2], yy[2], a0);
+                a1 = fmac(tt[3], yy[3], a1);
+            }
+            cplx d = sh.M[i * LDM + i] - lq;
+            if (abs2(d) < smallnum * smallnum) d = mkc(smallnum);
+            if (i < q && lane < 32) Yq[i] = -div_fast(a0 + a1, d);
+            wave_sync();
+        }
+        if (lane == 0) {
+            sh.total = total;
+            sh.failed = failed;
+        }
+    }
+    __syncthreads();
+    // ---- W = Z Y over T (8 columns at a time), and meanwhile the expansion
+    // x = Y^-1 Z^* alpha_1 of the POD coefficients of the first snapshot,
+    // alpha_1 = Sigma_r V_r^* e_1 (Sec. 3.3), in the columns of Z Y
+    if (wave == 3) {
+        const int q = lane & 31, hf = lane >> 5;
+        cplx al = mkc(0.0);
         if (q < k) {
-            const cplx lq = H[q + q * LDH];
-            for (int i = k - 1; i > q; --i) Y[i + q * LDH] = mkc(0.0);
-            Y[q + q * LDH] = mkc(1.0);
-            for (int i = q - 1; i >= 0; --i) {
-                cplx acc = mkc(0.0);
-                for (int j = i + 1; j <= q; ++j) acc = acc + H[i + j * LDH] * Y[j + q * LDH];
-                cplx d = H[i + i * LDH] - lq;
-                if (cabs(d) < smallnum) d = mkc(smallnum);
-                Y[i + q * LDH] = -cdiv(acc, d);
-            }
+            const cplx v0 = a.cplx ? cplx{a.V[2 * ((int64_t)q * ldv)], a.V[2 * ((int64_t)q * ldv) + 1]}
+                                   : mkc(a.V[(int64_t)q * ldv]);
+            al = sh.sig[q] * conj(v0);
         }
+        if (lane < 32) sh.x[q] = al;
+        wave_sync();
+        cplx g = mkc(0.0);
+        for (int i = 16 * hf; i < 16 * hf + 16; i += 4) {
+            cplx zz[4], xx[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                zz[u] = conj(sh.M[q * LDM + 32 + i + u]);
+                xx[u] = sh.x[i + u];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) g = fmac(zz[u], xx[u], g);
+        }
+        g = other_half_sum(g);
+        cplx yn = sh.Y[q + (k - 1) * LDH];
+        for (int jj = k - 1; jj >= 1; --jj) {
+            const cplx yc = yn;
+            yn = sh.Y[q + (jj - 1) * LDH];
+            const cplx xj = {lane_f64(g.re, jj), lane_f64(g.im, jj)};
+            if (q < jj) g = g - yc * xj;
+        }
+        wave_sync();
+        if (lane < 32) sh.x[q] = g;
     }
-    wave_sync();
-    // W = Z Y (lane = row), written over T
-    cplx lam_q = mkc(0.0);
-    if (lane < k) lam_q = H[lane + lane * LDH];
-    wave_sync();
+    __syncthreads();
     {
-        const int i = lane;
-        if (i < k) {
-            for (int q = 0; q < k; ++q) {
-                cplx acc = mkc(0.0);
-                for (int j = 0; j <= q; ++j) acc = acc + Z[i + j * LDH] * Y[j + q * LDH];
-                H[i + q * LDH] = acc;  // T is no longer needed
-            }
+        const int i = tid & 31;
+        cplx w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int q = (tid >> 5) + 8 * u;
+            w[u] = mkc(0.0);
+            if (q < k)
+                for (int j0 = 0; j0 <= q; j0 += 4) {
+                    cplx zz[4], yy[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        zz[e] = sh.M[(j0 + e) * LDM + 32 + i];
+                        yy[e] = j0 + e <= q ? sh.Y[j0 + e + q * LDH] : mkc(0.0);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[u] = fmac(zz[e], yy[e], w[u]);
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int q = (tid >> 5) + 8 * u;
+            if (q < k) sh.M[q * LDM + i] = w[u];  // (rows 0 .. 31: T is no longer needed)
         }
     }
-    wave_sync();
-    // normalise column q (lane q): unit norm, largest-modulus entry (lowest
-    // index on ties) real positive; rank by |lambda| descending, arg ascending
-    __shared__ cplx s_lam[kRMax];
-    __shared__ int s_partner[kRMax];
-    if (lane < k) s_lam[lane] = lam_q;
-    wave_sync();
-    if (!a.cplx) {
-        // A real A~ has a spectrum closed under conjugation.  The complex QR
-        // returns each conjugate pair with independent rounding; pair them
-        // up and make the member with negative imaginary part the exact
-        // conjugate of its partner (eigenvector too), and make numerically
-        // real eigenvalues exactly real, so that the order of eigenpairs does
-        // not depend on rounding.
-        const double dl = 1e-10;
+    __syncthreads();
+    if (wave == 0 && !a.cplx) {
+        // A real A~ has a spectrum closed under conjugation.  The two members
+        // of a conjugate pair come with independent rounding; pair them up
+        // and make the member with negative imaginary part the exact
+        // conjugate of its partner (eigenvector and expansion too), and make
+        // numerically real eigenvalues exactly real, so that the order of
+        // eigenpairs does not depend on rounding.
+        const double dl2 = 1e-20;
+        const bool live = lane < k;
+        const cplx lq = live ? sh.lam[lane] : mkc(0.0);
+        const double cut = dl2 * abs2(lq), im2 = lq.im * lq.im;
+        const bool neg = live && lq.im < 0.0 && im2 > cut, pos = live && lq.im > 0.0 && im2 > cut;
+        const unsigned long long mpos = __ballot(pos), mneg = __ballot(neg);
         int partner = -1;
-        if (lane < k && lam_q.im < -dl * cabs(lam_q)) {
-            double best = 1e300;
-            for (int p = 0; p < k; ++p) {
-                const cplx lp = s_lam[p];
-                if (!(lp.im > dl * cabs(lp))) continue;
-                const double d = cabs(conj(lp) - lam_q);
-                if (d < best) { best = d; partner = p; }
+        double best = 1e300;
+        for (int p = 0; p < k; ++p) {
+            const cplx lp = sh.lam[p];
+            const double d = sqr(lp.re - lq.re) + sqr(lp.im + lq.im);
+            if (neg && ((mpos >> p) & 1) && d < best) {
+                best = d;
+                partner = p;
             }
         }
-        if (lane < k) s_partner[lane] = partner;
-        wave_sync();
         // accept the pairing only if it is a bijection between the two halves
-        int npos = 0, nneg = 0, ok = 1;
-        for (int p = 0; p < k; ++p) {
-            const cplx lp = s_lam[p];
-            if (lp.im > dl * cabs(lp)) ++npos;
-            if (lp.im < -dl * cabs(lp)) {
-                ++nneg;
-                if (s_partner[p] < 0) ok = 0;
-                for (int q2 = 0; q2 < p; ++q2)
-                    if (s_partner[q2] == s_partner[p] && s_partner[p] >= 0) ok = 0;
-            }
-        }
-        ok = ok && (npos == nneg);
+        bool ok = __popcll(mpos) == __popcll(mneg) && __ballot(neg && partner < 0) == 0;
+        for (int p = 0; p < k; ++p) ok = ok && __popcll(__ballot(neg && partner == p)) <= 1;
         wave_sync();
-        if (ok && lane < k) {
-            const int pr = s_partner[lane];
-            if (pr >= 0) {
-                lam_q = conj(s_lam[pr]);
-                for (int i = 0; i < k; ++i) H[i + lane * LDH] = conj(H[i + pr * LDH]);
-            } else if (!(lam_q.im > dl * cabs(lam_q))) {
-                lam_q.im = 0.0;
+        if (ok && live) {
+            if (partner >= 0) {
+                sh.lam[lane] = conj(sh.lam[partner]);
+                sh.x[lane] = conj(sh.x[partner]);
+                for (int i = 0; i < k; ++i) sh.M[lane * LDM + i] = conj(sh.M[partner * LDM + i]);
+            } else if (!pos) {
+                sh.lam[lane].im = 0.0;
             }
         }
         wave_sync();
-        if (lane < k) s_lam[lane] = lam_q;
-        wave_sync();
     }
-    __shared__ double s_mod[kRMax], s_arg[kRMax];
-    __shared__ cplx s_ls[kRMax];  // eigenvalues in sorted order
-    if (lane < k) {
-        s_mod[lane] = cabs(lam_q);
-        s_arg[lane] = atan2(lam_q.im, lam_q.re);
+    __syncthreads();
+    if (tid < k) {
+        sh.mod[tid] = cabs(sh.lam[tid]);
+        sh.arg[tid] = atan2(sh.lam[tid].im, sh.lam[tid].re);
     }
-    wave_sync();
-    if (lane < k) {
-        const int q = lane;
+    __syncthreads();
+    // ---- normalise column q (8 lanes): unit norm, largest-modulus entry
+    // (lowest index on ties) real positive; rank by |lambda| descending, arg
+    // ascending; b = x / (scale lambda), the mode amplitudes (W Lambda)^-1 alpha_1
+    {
+        const int q = tid >> 3, e = tid & 7;
+        const bool live = q < k;
+        cplx w[4];
         double nrm2 = 0.0, best = -1.0;
-        int bi = 0;
-        for (int i = 0; i < k; ++i) {
-            const double v = abs2(H[i + q * LDH]);
+        int bi = 0, rank = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = e + 8 * u;
+            w[u] = live && i < k ? sh.M[q * LDM + i] : mkc(0.0);
+            const double v = abs2(w[u]);
             nrm2 += v;
-            if (v > best) { best = v; bi = i; }
+            if (i < k && v > best) {
+                best = v;
+                bi = i;
+            }
+            const double mq = sh.mod[live ? q : 0], aq = sh.arg[live ? q : 0];
+            if (i < k) {
+                const double mp = sh.mod[i], ap = sh.arg[i];
+                rank += (mp > mq) || (mp == mq && ap < aq) || (mp == mq && ap == aq && i < q);
+            }
         }
-        const cplx piv = H[bi + q * LDH];
-        const double ap = cabs(piv);
-        const cplx ph = ap > 0.0 ? cplx{piv.re / ap, -piv.im / ap} : mkc(1.0);
-        const cplx scale_q = (nrm2 > 0.0 ? 1.0 / sqrt(nrm2) : 1.0) * ph;
-        const double mq = s_mod[q], aq = s_arg[q];
-        int rank = 0;
-        for (int p = 0; p < k; ++p) {
-            const double mp = s_mod[p], app = s_arg[p];
-            rank += (mp > mq) || (mp == mq && app < aq) || (mp == mq && app == aq && p < q);
-        }
-        s_rank[q] = rank;
-        s_ls[rank] = lam_q;
-        a.lam[2 * rank] = lam_q.re;
-        a.lam[2 * rank + 1] = lam_q.im;
-        for (int i = 0; i < k; ++i) {
-            const cplx w = H[i + q * LDH] * scale_q;
-            Y[i + rank * LDH] = w;  // sorted, canonical W
-            a.W[2 * (i + (int64_t)rank * k)] = w.re;
-            a.W[2 * (i + (int64_t)rank * k) + 1] = w.im;
-        }
-    }
-    wave_sync();
-
-    // ---- mode amplitudes b = (W Lambda)^-1 alpha_1 (Sec. 3.3), alpha_1 = the
-    // POD coefficients of the first snapshot = Sigma_r V_r^* e_1 (first row
-    // of V_r); Gaussian elimination with partial pivoting on W Lambda (in H,
-    // free now), lanes over rows.  Then the background mode argmin |log
-    // lambda| (Algorithm 3) and its factor b_i lambda_i^m for the newest
-    // snapshot.
-    __shared__ cplx s_rhs[kRMax];
-    __shared__ cplx s_fbg;
-    __shared__ int s_bg;
-    for (int idx = lane; idx < k * k; idx += 64) {
-        const int i = idx % k, q = idx / k;
-        H[i + q * LDH] = Y[i + q * LDH] * s_ls[q];
-    }
-    if (lane < k) {
-        const cplx v0 = a.cplx ? cplx{a.V[2 * ((int64_t)lane * ldv)], a.V[2 * ((int64_t)lane * ldv) + 1]}
-                               : mkc(a.V[(int64_t)lane * ldv]);
-        s_rhs[lane] = s_sig[lane] * conj(v0);
-    }
-    wave_sync();
-    for (int c = 0; c < k; ++c) {
-        double best = -1.0;
-        int bi = c;
-        if (lane >= c && lane < k) {
-            best = abs2(H[lane + c * LDH]);
-            bi = lane;
-        }
-        for (int off = 32; off >= 1; off >>= 1) {
-            const double ob = __shfl_xor(best, off, 64);
-            const int oi = __shfl_xor(bi, off, 64);
-            if (ob > best || (ob == best && oi < bi)) {
-                best = ob;
+        auto lvl = [&](auto ctrl) {
+            constexpr int C = decltype(ctrl)::value;
+            nrm2 += dpp_f64<C>(nrm2);
+            rank += __builtin_amdgcn_mov_dpp(rank, C, 0xF, 0xF, true);
+            const double ov = dpp_f64<C>(best);
+            const int oi = __builtin_amdgcn_mov_dpp(bi, C, 0xF, 0xF, true);
+            if (ov > best || (ov == best && oi < bi)) {
+                best = ov;
                 bi = oi;
             }
-        }
-        if (bi != c) {
-            for (int j = lane; j < k; j += 64) {
-                const cplx t = H[c + j * LDH];
-                H[c + j * LDH] = H[bi + j * LDH];
-                H[bi + j * LDH] = t;
+        };
+        lvl(std::integral_constant<int, 0xB1>{});
+        lvl(std::integral_constant<int, 0x4E>{});
+        lvl(std::integral_constant<int, 0x141>{});
+        if (live) {
+            const cplx piv = sh.M[q * LDM + bi];
+            const double ap = cabs(piv);
+            const cplx ph = ap > 0.0 ? cplx{piv.re / ap, -piv.im / ap} : mkc(1.0);
+            const cplx scale_q = (nrm2 > 0.0 ? 1.0 / sqrt(nrm2) : 1.0) * ph;
+            const cplx lq = sh.lam[q];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = e + 8 * u;
+                if (i < k) {
+                    const cplx x = w[u] * scale_q;
+                    sh.Y[i + rank * LDH] = x;  // sorted, canonical W
+                    a.W[2 * (i + (int64_t)rank * k)] = x.re;
+                    a.W[2 * (i + (int64_t)rank * k) + 1] = x.im;
+                }
             }
-            if (lane == 0) {
-                const cplx t = s_rhs[c];
-                s_rhs[c] = s_rhs[bi];
-                s_rhs[bi] = t;
+            if (e == 0) {
+                sh.ls[rank] = lq;
+                a.lam[2 * rank] = lq.re;
+                a.lam[2 * rank + 1] = lq.im;
+                const cplx b = cdiv(sh.x[q], scale_q * lq);
+                a.amp[2 * rank] = b.re;
+                a.amp[2 * rank + 1] = b.im;
             }
         }
-        wave_sync();
-        const cplx piv = H[c + c * LDH];
-        if (lane > c && lane < k) {
-            const cplx f = cdiv(H[lane + c * LDH], piv);
-            for (int j = c + 1; j < k; ++j) H[lane + j * LDH] = H[lane + j * LDH] - f * H[c + j * LDH];
-            s_rhs[lane] = s_rhs[lane] - f * s_rhs[c];
-        }
-        wave_sync();
     }
-    for (int c = k - 1; c >= 0; --c) {
-        if (lane == 0) s_rhs[c] = cdiv(s_rhs[c], H[c + c * LDH]);
-        wave_sync();
-        if (lane < c) s_rhs[lane] = s_rhs[lane] - H[lane + c * LDH] * s_rhs[c];
-        wave_sync();
-    }
-    if (lane < k) {
-        a.amp[2 * lane] = s_rhs[lane].re;
-        a.amp[2 * lane + 1] = s_rhs[lane].im;
-    }
-    // background mode: lane q evaluates |log lambda_q|, then the smallest
-    // (lowest q on ties) over the lanes with lambda_q != 0; mode 0 if none
-    {
+    __syncthreads();
+    // ---- the background mode argmin |log lambda| (Algorithm 3; lowest index
+    // on ties, over lambda != 0; mode 0 if none) and its factor b_i lambda_i^m
+    // for the newest snapshot
+    if (wave == 0) {
         bool ok = false;
         double d = 0.0;
         if (lane < k) {
-            const cplx lq = s_ls[lane];
+            const cplx lq = sh.ls[lane];
             const double mod = cabs(lq);
             if (mod > 0.0) {
                 ok = true;
@@ -1104,24 +1127,23 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a) {
                 bi = oi;
             }
         }
-        if (lane == 0) s_bg = ok ? bi : 0;
+        bi = ok ? bi : 0;
+        if (lane == 0) {
+            sh.bg = bi;
+            st->bg_index = bi;
+            // lambda^m = |lambda|^m e^{i m arg lambda}
+            const cplx lb = sh.ls[bi];
+            const double pm = pow(cabs(lb), (double)m), th = (double)m * atan2(lb.im, lb.re);
+            sh.fbg = cplx{a.amp[2 * bi], a.amp[2 * bi + 1]} * cplx{pm * cos(th), pm * sin(th)};
+        }
     }
-    wave_sync();
-    if (lane == 0) {
-        const int bi = s_bg;
-        st->bg_index = bi;
-        // lambda^m = |lambda|^m e^{i m arg lambda}
-        const cplx lb = s_ls[bi];
-        const double pm = pow(cabs(lb), (double)m), th = (double)m * atan2(lb.im, lb.re);
-        s_fbg = s_rhs[bi] * cplx{pm * cos(th), pm * sin(th)};
-    }
-    wave_sync();
-    const int bgq = s_bg;
-    const cplx fbg = s_fbg;
+    __syncthreads();
+    const int bgq = sh.bg;
+    const cplx fbg = sh.fbg;
 
     // ---- C = V_r Sigma^-1 W (m x k complex), row-major with row stride 2 r;
-    // lane i keeps row i of V_r Sigma^-1 in registers, W (sorted) is in LDS
-    for (int i = lane; i < m; i += 64) {
+    // thread i keeps row i of V_r Sigma^-1 in registers, W (sorted) is in LDS
+    for (int i = tid; i < m; i += kEigThreads) {
         // (columns past k-1 read column k-1 and are zeroed: every load in flight at once)
         cplx vrow[kRMax];
 #pragma unroll
@@ -1130,7 +1152,7 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a) {
             cplx v;
             if (a.cplx) v = cplx{a.V[2 * (i + (int64_t)pc * ldv)], a.V[2 * (i + (int64_t)pc * ldv) + 1]};
             else v = mkc(a.V[i + (int64_t)pc * ldv]);
-            vrow[p] = p < k ? v * (1.0 / s_sig[pc]) : mkc(0.0);
+            vrow[p] = p < k ? v * (1.0 / sh.sig[pc]) : mkc(0.0);
         }
         // two columns q at a time: four independent accumulation chains (the
         // sums of each column keep their order)
@@ -1166,29 +1188,30 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a) {
 #pragma unroll
             for (int p = 0; p < kRMax; p += 2) {
                 if (p < k) {
-                    a0 = a0 + vrow[p] * Y[p + q * LDH];
-                    b0 = b0 + vrow[p] * Y[p + q1 * LDH];
+                    a0 = a0 + vrow[p] * sh.Y[p + q * LDH];
+                    b0 = b0 + vrow[p] * sh.Y[p + q1 * LDH];
                 }
                 if (p + 1 < k) {
-                    a1 = a1 + vrow[p + 1] * Y[p + 1 + q * LDH];
-                    b1 = b1 + vrow[p + 1] * Y[p + 1 + q1 * LDH];
+                    a1 = a1 + vrow[p + 1] * sh.Y[p + 1 + q * LDH];
+                    b1 = b1 + vrow[p + 1] * sh.Y[p + 1 + q1 * LDH];
                 }
             }
             emit(q, a0 + a1);
             if (q + 1 < k) emit(q + 1, b0 + b1);
         }
     }
-    if (lane == 0) {
-        st->qr_iters = total;
-        if (failed) st->solve_status = ST_E_CONVERGENCE;
+    if (tid == 0) {
+        st->qr_iters = sh.total;
+        if (sh.failed) st->solve_status = ST_E_CONVERGENCE;
         st->solves += 1;
     }
     publish(a);
 }
 
-__global__ __launch_bounds__(64)
+__global__ __launch_bounds__(kEigThreads, 2)
 void k_solve_eig(SolveArgs a) {
-    solve_eig_body(a);
+    __shared__ EigShared sh;
+    solve_eig_body(a, sh);
     if (a.snap_st) {
         // the snapshot of this solve (state and mode coefficients) for the
         // projections that may run beside the next push
@@ -1200,10 +1223,11 @@ void k_solve_eig(SolveArgs a) {
     }
 }
 
-__global__ __launch_bounds__(64)
+__global__ __launch_bounds__(kEigThreads, 2)
 void k_solve_eig_grouped(const SolveArgs* __restrict__ items) {
+    __shared__ EigShared sh;
     const SolveArgs a = items[blockIdx.x];
-    solve_eig_body(a);
+    solve_eig_body(a, sh);
 }
 
 // --------------------------------------------------------------------------
@@ -1708,7 +1732,7 @@ hipError_t launch_solve_trid_wide(const SolveArgs* one, const SolveArgs* items, 
 
 hipError_t launch_solve_eig(const SolveArgs& a, hipStream_t s) {
     if (a.r > kRMax) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_solve_eig, dim3(1), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(k_solve_eig, dim3(1), dim3(kEigThreads), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1718,7 +1742,7 @@ namespace dmd {
 
 hipError_t launch_eig_grouped(const SolveArgs* items, int n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_solve_eig_grouped, dim3(n), dim3(64), 0, s, items);
+    hipLaunchKernelGGL(k_solve_eig_grouped, dim3(n), dim3(kEigThreads), 0, s, items);
     return hipGetLastError();
 }
 
