@@ -1729,12 +1729,21 @@ struct TickLayout {
 // A tick replayed as a HIP graph: its launches depend only on these counts
 // and on the descriptor buffer, everything else reaches the kernels through
 // the descriptors that the graph's first node copies from pinned memory.
+// One chain of grouped launches: its Gram items, eigenproblems and projections
+// are consecutive in the tables, its block starts count from 0.
+struct TickChain {
+    int na = 0, gtot = 0, ns = 0, np = 0, ptot = 0;
+    size_t plds = 0;  // LDS of the grouped projection
+    bool operator==(const TickChain& o) const {
+        return na == o.na && gtot == o.gtot && ns == o.ns && np == o.np && ptot == o.ptot && plds == o.plds;
+    }
+};
 struct TickShape {
-    int buf, count, nl, ng, nt[3], gtot, np, ptot;
-    size_t plds;
+    int buf, nl, ng, nt[3];
+    TickChain chain[2];
     bool operator==(const TickShape& o) const {
-        return buf == o.buf && count == o.count && nl == o.nl && ng == o.ng && nt[0] == o.nt[0] && nt[1] == o.nt[1] &&
-               nt[2] == o.nt[2] && gtot == o.gtot && np == o.np && ptot == o.ptot && plds == o.plds;
+        return buf == o.buf && nl == o.nl && ng == o.ng && nt[0] == o.nt[0] && nt[1] == o.nt[1] && nt[2] == o.nt[2] &&
+               chain[0] == o.chain[0] && chain[1] == o.chain[1];
     }
 };
 struct TickGraph {
@@ -1751,6 +1760,8 @@ struct dmd_batch {
     std::vector<TickGraph> tick_graphs;
     uint64_t uses = 0;
     hipStream_t cap_stream = nullptr;  // capture stream (default priority)
+    hipStream_t side = nullptr;        // the wide windows' chain of a tick (default priority)
+    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     int64_t budget = 0, used = 0;
     std::vector<dmd_stream*> members;
     TickLayout L{};
@@ -1778,6 +1789,9 @@ static void batch_free(dmd_batch* b) {
     }
     b->tick_graphs.clear();
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
+    if (b->side) (void)hipStreamDestroy(b->side);
+    if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
+    if (b->ev_join) (void)hipEventDestroy(b->ev_join);
     for (int i = 0; i < 2; ++i) {
         if (b->host[i]) (void)hipHostFree(b->host[i]);
         if (b->dev[i]) (void)hipFree(b->dev[i]);
@@ -1826,6 +1840,9 @@ DMD_API int dmd_batch_create(const dmd_batch_opts_t* opts, dmd_batch_t** out) {
     }
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_last, hipEventDisableTiming);
     if (e == hipSuccess && b->graphs > 0) e = hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_join, hipEventDisableTiming);
     if (e != hipSuccess) {
         batch_free(b);
         delete b;
@@ -1937,56 +1954,76 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
     auto* sa = reinterpret_cast<dmd::SolveArgs*>(H + b->L.all);
     auto* pa = reinterpret_cast<dmd::ProjectArgs*>(H + b->L.proj);
     int* pblk = reinterpret_cast<int*>(H + b->L.pblk);
-    int na = 0, nl = 0, ng = 0, np = 0, gtot = 0, ptot = 0;
-    size_t plds = 0;  // LDS of the grouped projection
+    int nl = 0, ng = 0;
     int nt[3] = {0, 0, 0}, nc[3] = {0, 0, 0};  // tridiagonal solves by size class, real and Hermitian
     std::vector<int> own;  // members that run their own Gram and projection kernels
+    auto grouped = [](const dmd_stream* h) { return !h->cplx && h->elem_bytes == 4 && !h->coef_f64; };
+    auto wide = [](const dmd_stream* h) { return h->use_trid && dmd::trid_class(h->m, false) > 0; };
+    // Two chains: the windows past the smallest class of the tridiagonal solve
+    // (m > 64) first, on the side stream from their solves on, the others
+    // behind their Gram pass on the tick's stream.  The solves keep a workgroup
+    // per window busy and leave the memory idle: a wide window's
+    // (reduction, values, vectors and eig in turn, about 700 us at m = 128, r =
+    // 32) run beside the other members' Gram pass and solves.  One chain where
+    // the members are all of one kind, or where one runs kernels of its own
+    // (its solve is in the same tables).  24 unlike windows (m = 16 .. 128):
+    // 3501 us in one chain, 3143 in two.
+    int nwide = 0, ngrouped = 0;
     for (int i = 0; i < count; ++i) {
-        dmd_stream* h = streams[i];
-        const bool grouped = !h->cplx && h->elem_bytes == 4 && !h->coef_f64;
-        if (grouped) {
-            dmd::GramItem& it = gi[na];
-            it = dmd::GramItem{};
-            it.x = frames[i].x;
-            it.ring = h->ring;
-            it.ld = h->ld;
-            it.n = h->n;
-            it.m = h->m;
-            it.slots = h->slots;
-            it.x_aligned = ((uintptr_t)frames[i].x % 16) == 0;
-            it.iter = h->gram_iter;
-            it.nblk = dmd::gram_blocks(h->n, h->elem_bytes, h->gram_iter);
-            it.partials = h->partials;
-            it.G = h->G;
-            it.st = reinterpret_cast<DevState*>(h->res_dev);
-            gblk[na] = gtot;
-            gtot += it.nblk;
-            ++na;
-            if (modes && modes[i]) {
-                fill_project_args(h, pa[np], modes[i], ld_modes[i], true);
-                pblk[np] = ptot;
-                ptot += dmd::project_item_blocks(h->n);
-                plds = std::max(plds, dmd::project_item_lds(pa[np]));
-                ++np;
+        ngrouped += grouped(streams[i]);
+        nwide += grouped(streams[i]) && wide(streams[i]);
+    }
+    const bool fork = ngrouped == count && nwide > 0 && nwide < count;
+    TickChain ch[2];  // [1]: the wide windows of a forked tick, first in the tables
+    for (int pass = fork ? 1 : 0; pass >= 0; --pass) {
+        TickChain& c = ch[pass];
+        for (int i = 0; i < count; ++i) {
+            dmd_stream* h = streams[i];
+            if (fork && wide(h) != (pass == 1)) continue;
+            if (grouped(h)) {
+                const int at = (pass == 0 ? ch[1].na : 0) + c.na;
+                dmd::GramItem& it = gi[at];
+                it = dmd::GramItem{};
+                it.x = frames[i].x;
+                it.ring = h->ring;
+                it.ld = h->ld;
+                it.n = h->n;
+                it.m = h->m;
+                it.slots = h->slots;
+                it.x_aligned = ((uintptr_t)frames[i].x % 16) == 0;
+                it.iter = h->gram_iter;
+                it.nblk = dmd::gram_blocks(h->n, h->elem_bytes, h->gram_iter);
+                it.partials = h->partials;
+                it.G = h->G;
+                it.st = reinterpret_cast<DevState*>(h->res_dev);
+                gblk[at] = c.gtot;
+                c.gtot += it.nblk;
+                ++c.na;
+                if (modes && modes[i]) {
+                    const int pt = (pass == 0 ? ch[1].np : 0) + c.np;
+                    fill_project_args(h, pa[pt], modes[i], ld_modes[i], true);
+                    pblk[pt] = c.ptot;
+                    c.ptot += dmd::project_item_blocks(h->n);
+                    c.plds = std::max(c.plds, dmd::project_item_lds(pa[pt]));
+                    ++c.np;
+                }
+            } else {
+                own.push_back(i);
             }
-        } else {
-            own.push_back(i);
-        }
-        dmd::SolveArgs a;
-        fill_solve_args(h, a);
-        sa[i] = a;
-        if (h->use_trid) {
-            const int c = dmd::trid_class(h->m, h->cplx);
-            const size_t off = h->cplx ? b->L.ctrid[c] : b->L.trid[c];
-            reinterpret_cast<dmd::SolveArgs*>(H + off)[h->cplx ? nc[c]++ : nt[c]++] = a;
-        } else if (h->m + (h->m & 1) <= 64) {
-            sl[nl++] = a;
-        } else {
-            sg[ng++] = a;
+            dmd::SolveArgs a;
+            fill_solve_args(h, a);
+            sa[(pass == 0 ? ch[1].ns : 0) + c.ns++] = a;
+            if (h->use_trid) {
+                const int k = dmd::trid_class(h->m, h->cplx);
+                const size_t off = h->cplx ? b->L.ctrid[k] : b->L.trid[k];
+                reinterpret_cast<dmd::SolveArgs*>(H + off)[h->cplx ? nc[k]++ : nt[k]++] = a;
+            } else if (h->m + (h->m & 1) <= 64) {
+                sl[nl++] = a;
+            } else {
+                sg[ng++] = a;
+            }
         }
     }
-    gblk[na] = gtot;
-    pblk[np] = ptot;
     // order after every member's earlier work and the batch's previous tick
     for (int i = 0; i < count; ++i) HIP_TRY(begin(streams[i], s));
     if (b->has_last && b->last_stream != s) HIP_TRY(hipStreamWaitEvent(s, b->ev_last, 0));
@@ -2030,42 +2067,73 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
         hipError_t e = hipMemcpyAsync(D, H, b->L.bytes, hipMemcpyHostToDevice, q);
         if (e != hipSuccess) return e;
         auto phase = [&](const char* name, auto&& fn) { return time_phases ? timed(name, q, fn) : fn(); };
-        auto* dgi = reinterpret_cast<const dmd::GramItem*>(D + b->L.gram);
-        auto* dgblk = reinterpret_cast<const int*>(D + b->L.gblk);
+        auto chain_gram = [&](int c) -> hipError_t {
+            const int at = c == 0 ? ch[1].na : 0;
+            if (ch[c].na == 0) return hipSuccess;
+            return dmd::launch_gram_grouped(reinterpret_cast<const dmd::GramItem*>(D + b->L.gram) + at,
+                                            reinterpret_cast<const int*>(D + b->L.gblk) + at, ch[c].na, ch[c].gtot, q);
+        };
+        auto chain_eig = [&](int c, hipStream_t t) -> hipError_t {
+            return dmd::launch_eig_grouped(
+                reinterpret_cast<const dmd::SolveArgs*>(D + b->L.all) + (c == 0 ? ch[1].ns : 0), ch[c].ns, t);
+        };
+        auto chain_project = [&](int c, hipStream_t t) -> hipError_t {
+            const int at = c == 0 ? ch[1].np : 0;
+            if (ch[c].np == 0) return hipSuccess;
+            return dmd::launch_project_grouped(reinterpret_cast<const dmd::ProjectArgs*>(D + b->L.proj) + at,
+                                               reinterpret_cast<const int*>(D + b->L.pblk) + at, ch[c].np, ch[c].ptot,
+                                               ch[c].plds, t);
+        };
+        const dmd::SolveArgs *rl[3], *cl[3];
+        for (int c = 0; c < 3; ++c) {
+            rl[c] = reinterpret_cast<const dmd::SolveArgs*>(D + b->L.trid[c]);
+            cl[c] = reinterpret_cast<const dmd::SolveArgs*>(D + b->L.ctrid[c]);
+        }
+        const int narrow[3] = {nt[0], fork ? 0 : nt[1], fork ? 0 : nt[2]};
         e = phase("batch_gram", [&] {
-            hipError_t f = na > 0 ? dmd::launch_gram_grouped(dgi, dgblk, na, gtot, q) : hipSuccess;
+            hipError_t f = hipSuccess;
+            if (fork) {
+                const int rest[3] = {0, nt[1], nt[2]};
+                f = chain_gram(1);
+                if (f == hipSuccess) f = hipEventRecord(b->ev_fork, q);
+                if (f == hipSuccess) f = hipStreamWaitEvent(b->side, b->ev_fork, 0);
+                if (f == hipSuccess) f = dmd::launch_trid_grouped(rl, rest, b->side);
+                if (f == hipSuccess) f = chain_eig(1, b->side);
+                if (f == hipSuccess) f = chain_project(1, b->side);
+                // (joined below on every path: a capture must not end with the side stream in it)
+                const hipError_t r = hipEventRecord(b->ev_join, b->side);
+                if (f == hipSuccess) f = r;
+            }
+            if (f == hipSuccess) f = chain_gram(0);
             for (size_t u = 0; u < own.size() && f == hipSuccess; ++u) f = own_gram(q, own[u]);
             return f;
         });
-        if (e != hipSuccess) return e;
-        e = phase("batch_solve", [&] {
-            hipError_t f = dmd::launch_jacobi_grouped(reinterpret_cast<const dmd::SolveArgs*>(D + b->L.lds), nl,
-                                                      reinterpret_cast<const dmd::SolveArgs*>(D + b->L.glb), ng, q);
-            const dmd::SolveArgs *rl[3], *cl[3];
-            for (int c = 0; c < 3; ++c) {
-                rl[c] = reinterpret_cast<const dmd::SolveArgs*>(D + b->L.trid[c]);
-                cl[c] = reinterpret_cast<const dmd::SolveArgs*>(D + b->L.ctrid[c]);
-            }
-            if (f == hipSuccess) f = dmd::launch_trid_grouped(rl, nt, q);
-            if (f == hipSuccess) f = dmd::launch_trid_grouped_cplx(cl, nc, q);
-            if (f == hipSuccess)
-                f = dmd::launch_eig_grouped(reinterpret_cast<const dmd::SolveArgs*>(D + b->L.all), count, q);
-            return f;
-        });
-        if (e != hipSuccess || !modes) return e;
-        return phase("batch_project", [&] {
-            hipError_t f = np > 0 ? dmd::launch_project_grouped(reinterpret_cast<const dmd::ProjectArgs*>(D + b->L.proj),
-                                                                reinterpret_cast<const int*>(D + b->L.pblk), np, ptot, plds, q)
-                                  : hipSuccess;
-            for (size_t u = 0; u < own.size() && f == hipSuccess; ++u) f = own_project(q, own[u]);
-            return f;
-        });
+        if (e == hipSuccess)
+            e = phase("batch_solve", [&] {
+                hipError_t f = dmd::launch_jacobi_grouped(reinterpret_cast<const dmd::SolveArgs*>(D + b->L.lds), nl,
+                                                          reinterpret_cast<const dmd::SolveArgs*>(D + b->L.glb), ng, q);
+                if (f == hipSuccess) f = dmd::launch_trid_grouped(rl, narrow, q);
+                if (f == hipSuccess) f = dmd::launch_trid_grouped_cplx(cl, nc, q);
+                if (f == hipSuccess) f = chain_eig(0, q);
+                return f;
+            });
+        if (e == hipSuccess && modes)
+            e = phase("batch_project", [&] {
+                hipError_t f = chain_project(0, q);
+                for (size_t u = 0; u < own.size() && f == hipSuccess; ++u) f = own_project(q, own[u]);
+                return f;
+            });
+        if (fork) {
+            const hipError_t f = hipStreamWaitEvent(q, b->ev_join, 0);
+            if (e == hipSuccess) e = f;
+        }
+        return e;
     };
     // graph replays take every per-tick value from the descriptors; members
     // with kernels of their own pass their frames as launch arguments, so
     // such ticks run eagerly
     if (b->graphs > 0 && own.empty()) {
-        const TickShape shape{buf, count, nl, ng, {nt[0], nt[1], nt[2]}, gtot, np, ptot, plds};
+        const TickShape shape{buf, nl, ng, {nt[0], nt[1], nt[2]}, {ch[0], ch[1]}};
         TickGraph* tg = nullptr;
         for (TickGraph& g : b->tick_graphs)
             if (g.shape == shape) tg = &g;
