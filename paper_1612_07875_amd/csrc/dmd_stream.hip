@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -109,6 +110,15 @@ hipError_t timed(const char* name, hipStream_t s, F&& launch) {
 
 }  // namespace
 
+// An event that the members of a tick share: recorded once behind the tick, and
+// recorded again only when no member refers to it any more.
+struct SharedEvent {
+    hipEvent_t ev = nullptr;
+    ~SharedEvent() {
+        if (ev) (void)hipEventDestroy(ev);
+    }
+};
+
 struct dmd_stream {
     int64_t n = 0, ld = 0;
     int32_t m = 0, r = 0, slots = 0;
@@ -207,6 +217,10 @@ struct dmd_stream {
 
     hipEvent_t ev_last = nullptr;
     hipEvent_t ev_solved = nullptr;
+    // set by a tick, until the handle's own work records the events above again
+    std::shared_ptr<SharedEvent> tick_last, tick_solved;
+    hipEvent_t last_event() const { return tick_last ? tick_last->ev : ev_last; }
+    hipEvent_t solved_event() const { return tick_solved ? tick_solved->ev : ev_solved; }
     hipStream_t last_stream = nullptr;
     bool has_last = false;
     bool solve_enqueued = false;
@@ -233,7 +247,7 @@ hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 // for everything enqueued before it.
 hipError_t begin(dmd_stream* h, hipStream_t s) {
     if (h->has_last && h->last_stream != s) {
-        hipError_t e = hipStreamWaitEvent(s, h->ev_last, 0);
+        hipError_t e = hipStreamWaitEvent(s, h->last_event(), 0);
         if (e != hipSuccess) return e;
     }
     for (int p = 0; p < 2; ++p) {
@@ -253,7 +267,7 @@ hipError_t begin(dmd_stream* h, hipStream_t s) {
 // of that solve (not the slot this push writes) and its snapshot only.
 hipError_t begin_single(dmd_stream* h, hipStream_t s, int p) {
     if (h->has_last && h->last_stream != s) {
-        hipError_t e = hipStreamWaitEvent(s, h->ev_last, 0);
+        hipError_t e = hipStreamWaitEvent(s, h->last_event(), 0);
         if (e != hipSuccess) return e;
     }
     for (int q = 0; q < 2; ++q)
@@ -269,7 +283,7 @@ hipError_t begin_single(dmd_stream* h, hipStream_t s, int p) {
 // writes nor its packed inputs.
 hipError_t begin_block(dmd_stream* h, hipStream_t s, int p) {
     if (h->has_last && h->last_stream != s) {
-        hipError_t e = hipStreamWaitEvent(s, h->ev_last, 0);
+        hipError_t e = hipStreamWaitEvent(s, h->last_event(), 0);
         if (e != hipSuccess) return e;
     }
     for (int q = 0; q < 2; ++q)
@@ -283,6 +297,7 @@ hipError_t begin_block(dmd_stream* h, hipStream_t s, int p) {
 hipError_t end(dmd_stream* h, hipStream_t s) {
     h->last_stream = s;
     h->has_last = true;
+    h->tick_last.reset();
     return hipEventRecord(h->ev_last, s);
 }
 
@@ -473,6 +488,7 @@ int enqueue_solve(dmd_stream* h, hipStream_t s, bool sym_done = false) {
         h->snap_par = par;
         ++h->snap_seq;
     }
+    h->tick_solved.reset();
     HIP_TRY(hipEventRecord(h->ev_solved, s));
     h->solve_enqueued = true;
     return DMD_OK;
@@ -480,7 +496,7 @@ int enqueue_solve(dmd_stream* h, hipStream_t s, bool sym_done = false) {
 
 int wait_solved(dmd_stream* h) {
     if (!h->solve_enqueued) return fail(DMD_E_NOT_READY, "no solve has been enqueued");
-    HIP_TRY(hipEventSynchronize(h->ev_solved));
+    HIP_TRY(hipEventSynchronize(h->solved_event()));
     return DMD_OK;
 }
 
@@ -505,7 +521,7 @@ int solve_status(dmd_stream* h) {
 }
 
 int read_state(dmd_stream* h, DevState* out) {
-    if (h->has_last) HIP_TRY(hipEventSynchronize(h->ev_last));
+    if (h->has_last) HIP_TRY(hipEventSynchronize(h->last_event()));
     HIP_TRY(hipMemcpy(out, h->res_dev, sizeof(DevState), hipMemcpyDeviceToHost));
     return DMD_OK;
 }
@@ -763,7 +779,7 @@ DMD_API int dmd_stream_footprint(int64_t n, int32_t m, int32_t r, const dmd_opts
 DMD_API int dmd_stream_destroy(dmd_stream_t* h) {
     if (!h) return DMD_OK;
     DeviceGuard g(h->device);
-    if (h->has_last) (void)hipEventSynchronize(h->ev_last);
+    if (h->has_last) (void)hipEventSynchronize(h->last_event());
     for (int p = 0; p < 2; ++p) {
         if (h->proj_pending[p]) (void)hipEventSynchronize(h->ev_proj[p]);
         if (h->sproj_pending[p]) (void)hipEventSynchronize(h->ev_sproj[p]);
@@ -969,6 +985,7 @@ DMD_API int dmd_stream_push_block(dmd_stream_t* h, const void* X_new, int64_t ld
                                        : dmd::launch_jacobi_grouped(t, lds ? k : 0, t, lds ? 0 : k, s);
             return e != hipSuccess ? e : dmd::launch_eig_grouped(t, k, s);
         }));
+        h->tick_solved.reset();
         HIP_TRY(hipEventRecord(h->ev_solved, s));
         h->solve_enqueued = true;
         h->last_block_k = k;
@@ -1030,7 +1047,7 @@ DMD_API int dmd_stream_block_modes(dmd_stream_t* h, void* phi, int64_t ld, int64
         // packed after its solves: ordered after the push, not after later
         // calls' other work; later calls that touch those inputs wait for it
         const int par = h->last_packed;
-        if (h->has_last && h->last_stream != s) HIP_TRY(hipStreamWaitEvent(s, h->ev_last, 0));
+        if (h->has_last && h->last_stream != s) HIP_TRY(hipStreamWaitEvent(s, h->last_event(), 0));
         if (h->proj_pending[par] && h->proj_stream[par] != s) HIP_TRY(hipStreamWaitEvent(s, h->ev_proj[par], 0));
         dmd::BlockProjectArgs a;
         fill_block_project_args(h, a, k, par);
@@ -1195,7 +1212,7 @@ DMD_API int dmd_stream_fourier_setup(dmd_stream_t* h, int32_t height, int32_t wi
     if (width > dmd::kFourierMaxW) return fail(DMD_E_INVAL, "width must be <= %d", dmd::kFourierMaxW);
     if (nkeep < 1 || nkeep > h->max_nnz) return fail(DMD_E_INVAL, "nkeep must be in [1, max_nnz=%d]", h->max_nnz);
     DeviceGuard g(h->device);
-    if (h->has_last) HIP_TRY(hipEventSynchronize(h->ev_last));  // buffers may be in use by earlier pushes
+    if (h->has_last) HIP_TRY(hipEventSynchronize(h->last_event()));  // buffers may be in use by earlier pushes
     free_fourier(h);
     // the nkeep bins of smallest ky^2 + kx^2 (signed), ties by flattened index
     const int64_t n = h->n;
@@ -1524,7 +1541,7 @@ static int project(dmd_stream_t* h, void* out, int64_t ld, void* stream, bool mo
     if (modes && h->snap_par >= 0) {
         // the latest solve's snapshot: after that solve, beside the next push
         const int par = h->snap_par;
-        if (h->has_last && h->last_stream != s) HIP_TRY(hipStreamWaitEvent(s, h->ev_last, 0));
+        if (h->has_last && h->last_stream != s) HIP_TRY(hipStreamWaitEvent(s, h->last_event(), 0));
         if (h->sproj_pending[par] && h->sproj_stream[par] != s) HIP_TRY(hipStreamWaitEvent(s, h->ev_sproj[par], 0));
         a.st = h->snap_st + par;
         a.B = h->snap_B + par * h->snap_B_bytes;
@@ -1762,6 +1779,7 @@ struct dmd_batch {
     hipStream_t cap_stream = nullptr;  // capture stream (default priority)
     hipStream_t side = nullptr;        // the wide windows' chain of a tick (default priority)
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    std::vector<std::shared_ptr<SharedEvent>> events;  // at most one per member, and one
     int64_t budget = 0, used = 0;
     std::vector<dmd_stream*> members;
     TickLayout L{};
@@ -1967,7 +1985,7 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
     // 32) run beside the other members' Gram pass and solves.  One chain where
     // the members are all of one kind, or where one runs kernels of its own
     // (its solve is in the same tables).  24 unlike windows (m = 16 .. 128):
-    // 3501 us in one chain, 3143 in two.
+    // 3501 us in one chain, 3143 in two (both with two events per member recorded behind the tick).
     int nwide = 0, ngrouped = 0;
     for (int i = 0; i < count; ++i) {
         ngrouped += grouped(streams[i]);
@@ -2175,14 +2193,26 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
     HIP_TRY(hipEventRecord(b->done[buf], s));
     b->used_buf[buf] = true;
     b->next ^= 1;
+    // one event for all members: an event record is a barrier on the stream
+    // (3 to 4 us each; two of its own per member took about 230 us of 24)
+    std::shared_ptr<SharedEvent> ev;
+    for (auto& p : b->events)
+        if (p.use_count() == 1) ev = p;
+    if (!ev) {
+        ev = std::make_shared<SharedEvent>();
+        HIP_TRY(hipEventCreateWithFlags(&ev->ev, hipEventDisableTiming));
+        b->events.push_back(ev);
+    }
+    HIP_TRY(hipEventRecord(ev->ev, s));
     for (int i = 0; i < count; ++i) {
         dmd_stream* h = streams[i];
-        HIP_TRY(hipEventRecord(h->ev_solved, s));
+        h->tick_last = h->tick_solved = ev;
+        h->last_stream = s;
+        h->has_last = true;
         h->solve_enqueued = true;
         h->last_block_k = 0;
         h->last_packed = -1;
         h->snap_par = -1;
-        HIP_TRY(end(h, s));
     }
     b->last_stream = s;
     b->has_last = true;
