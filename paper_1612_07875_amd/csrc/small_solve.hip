@@ -1335,7 +1335,7 @@ __device__ void householder_col(S* A, int ld, int n, int j, S* vbuf, S* s_tau, d
     }
 }
 
-template <typename S, int NT, bool LDS>
+template <typename S, int NT>
 __device__ void solve_trid_body(const SolveArgs& a) {
     using SC = Scal<S>;
     extern __shared__ double dyn[];
@@ -1366,12 +1366,12 @@ __device__ void solve_trid_body(const SolveArgs& a) {
     __shared__ double s_zsc[kRMax];
     __shared__ double s_scale;
 
-    // storage: A (n x ld) in LDS for small windows, else in the workspace;
-    // the multipliers of the twisted factorizations (2 n nv doubles) in LDS,
+    // storage: A (n x ld) in the workspace; the multipliers of the twisted
+    // factorizations (2 n nv doubles) in LDS,
     // later the eigenvectors during the back-transformation; Z (n x nv) and
     // the tail's scratch after A in the workspace
-    S* A = LDS ? reinterpret_cast<S*>(dyn) : reinterpret_cast<S*>(a.work);
-    double* LU = LDS ? dyn + (size_t)n * ld * (sizeof(S) / sizeof(double)) : dyn;
+    S* A = reinterpret_cast<S*>(a.work);
+    double* LU = dyn;
     S* Z = reinterpret_cast<S*>(a.work) + (size_t)n * ld;
     S* spare1 = Z + (size_t)n * ld;
     S* spare2 = spare1 + (size_t)n * ld;
@@ -1402,7 +1402,7 @@ __device__ void solve_trid_body(const SolveArgs& a) {
             const int gi = tid / G, gl = tid % G;
             for (int i = gi; i < L; i += NT / G) {
                 const S* ci = A22 + (size_t)i * ld;
-                S acc = ordered_dot<kAhead<S, LDS>>(SC::zero(), gl, G, L, [&](int k) { return SC::cj(ci[k]); },
+                S acc = ordered_dot<kAhead<S, false>>(SC::zero(), gl, G, L, [&](int k) { return SC::cj(ci[k]); },
                                        [&](int k) { return v[k]; });
                 acc = group_sum(acc, G);
                 if (gl == 0) s_p[i] = mulr(tau, acc);
@@ -1435,7 +1435,7 @@ __device__ void solve_trid_body(const SolveArgs& a) {
                 return a - (mulr(vk, SC::cj(wi)) + mulr(wk, SC::cj(vi)));
             };
             auto at = [&](int idx) -> S& { return A22[(1 + idx % L1) + (size_t)(1 + idx / L1) * ld]; };
-            constexpr int U = LDS ? 1 : 4;
+            constexpr int U = 4;
             int idx = tid - 64;
             if constexpr (U > 1) {
                 for (; idx + (U - 1) * NW < L1 * L1; idx += U * NW) {
@@ -1685,17 +1685,17 @@ __device__ void solve_trid_body(const SolveArgs& a) {
     // eigenvector index k of the tail = selection rank k (columns of Z)
     for (int i = tid; i < n; i += NT) s_perm[i] = i;
     __syncthreads();
-    sym_tail<S, NT, kAhead<S, LDS>>(a, ld, Z, spare1, spare2, s_sig, s_perm, nv, 0, true, 0);
+    sym_tail<S, NT, kAhead<S, false>>(a, ld, Z, spare1, spare2, s_sig, s_perm, nv, 0, true, 0);
 }
 
 __global__ __launch_bounds__(1024)
 void k_solve_trid_wide(SolveArgs a) {
-    solve_trid_body<cplx, 1024, false>(a);
+    solve_trid_body<cplx, 1024>(a);
 }
 __global__ __launch_bounds__(1024)
 void k_solve_trid_wide_grouped(const SolveArgs* __restrict__ items) {
     const SolveArgs a = items[blockIdx.x];
-    solve_trid_body<cplx, 1024, false>(a);
+    solve_trid_body<cplx, 1024>(a);
 }
 
 }  // namespace
