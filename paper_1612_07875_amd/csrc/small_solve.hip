@@ -518,7 +518,7 @@ void k_solve_sym_grouped(const SolveArgs* __restrict__ items) {
 // 24 windows of a tick 878 -> 462.
 // --------------------------------------------------------------------------
 constexpr int LDM = 65;
-constexpr int kEigCols = 40;  // 32, and the (zero) columns that a run of eight may reach past them
+constexpr int kEigCols = 39;  // 32, and the (zero) columns that a run of eight may reach past them
 constexpr int kEigThreads = 256;
 constexpr int LDH = kRMax + 1;  // column stride of the eigenvector matrices
 
@@ -627,9 +627,9 @@ __device__ __forceinline__ int deflate(S* M, int hi, int lane, double hmax) {
 // (x + sign(x) s, y, z), s = ||(x, y, z)||, tau = 1 / (s (s + |x|)), by the
 // hardware estimates plus Newton steps), the three rows (lane = column), LDS,
 // the three columns (lane = row of H or Z), and the next (x, y, z) from the
-// lanes that hold them.  About 80 instructions, 450 cycles measured; with the
-// rows of Z apart from H's, masked writes and 2 / v^T v summed up it took
-// 1000 to 1200.
+// lanes that hold them.  22 sweeps of a 20 x 20 matrix take 68 us, deflation
+// checks included (about 700 cycles a step); with the rows of Z apart from H's,
+// masked writes and 2 / v^T v summed up a step took 1000 to 1200.
 __device__ __forceinline__ void real_schur(double* M, int k, int lane, int max_iter, double hmax, int& total,
                                            bool& failed) {
     auto h = [&](int i, int j) -> double& { return M[j * LDM + i]; };
@@ -833,10 +833,86 @@ struct EigShared {
     };
     cplx lam[kRMax], ls[kRMax];              // eigenvalues: Schur order, sorted
     cplx x[kRMax];                           // expansion of alpha_1 in the unscaled eigenvectors
-    double mod[kRMax], arg[kRMax], sig[kRMax];
+    double mod[kRMax], arg[kRMax], sig[kRMax], isig[kRMax];
     cplx fbg;
     int bg, total, failed;
 };
+
+// C = V_r Sigma^-1 W: a thread keeps a row of V_r Sigma^-1 in registers, W
+// (sorted) is in LDS.  Windows of up to 64 (128) columns have four (two)
+// threads for a row, each with its share of the columns of C; several rows of W for two
+// columns are read at a time.  m = 64, r = 20 / 32: 26 / 55 us with a thread
+// per row, complex rows for real V and one row of W at a time.
+template <typename S>
+__device__ __forceinline__ void coef_rows(const SolveArgs& a, EigShared& sh, int m, int k) {
+    using SC = Scal<S>;
+    constexpr int U = sizeof(S) == sizeof(cplx) ? 2 : 4;  // rows of W read at a time (registers)
+    const int ldv = a.m, bgq = sh.bg;
+    const cplx fbg = sh.fbg;
+    const int parts = m <= 64 ? 4 : m <= 128 ? 2 : 1, rows = kEigThreads / parts;
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x / rows);
+    for (int i = threadIdx.x % rows; i < m; i += rows) {
+        // (columns past k-1 read column k-1 and are zeroed: every load in flight at once)
+        S vrow[kRMax];
+#pragma unroll
+        for (int p = 0; p < kRMax; ++p) {
+            vrow[p] = reinterpret_cast<const S*>(a.V)[(unsigned)((p < k ? p : k - 1) * ldv) + (unsigned)i];
+        }
+#pragma unroll
+        for (int p = 0; p < kRMax; ++p) vrow[p] = p < k ? vrow[p] * sh.isig[p] : SC::zero();
+        auto emit = [&](int q, const cplx& acc) {
+            if (q == bgq && a.Bbg) {
+                // background coefficients beta_i = C[i][bg] b_bg lambda_bg^m
+                const cplx bt = acc * fbg;
+                if (a.coef_f64) {
+                    reinterpret_cast<double*>(a.Bbg)[2 * i] = bt.re;
+                    reinterpret_cast<double*>(a.Bbg)[2 * i + 1] = bt.im;
+                } else {
+                    reinterpret_cast<float*>(a.Bbg)[2 * i] = (float)bt.re;
+                    reinterpret_cast<float*>(a.Bbg)[2 * i + 1] = (float)bt.im;
+                }
+            }
+            const int64_t o = (int64_t)i * 2 * a.r + 2 * q;
+            if (a.coef_f64) {
+                double* B = reinterpret_cast<double*>(a.Bphi);
+                B[o] = acc.re;
+                B[o + 1] = acc.im;
+            } else {
+                float* B = reinterpret_cast<float*>(a.Bphi);
+                B[o] = (float)acc.re;
+                B[o + 1] = (float)acc.im;
+            }
+        };
+        for (int q = 2 * part; q < k; q += 2 * parts) {
+            const cplx* w0 = sh.Y + q * LDH;
+            const cplx* w1 = sh.Y + (q + 1 < k ? q + 1 : q) * LDH;
+            cplx a0 = mkc(0.0), a1 = mkc(0.0), b0 = mkc(0.0), b1 = mkc(0.0);
+            each_i<0, kRMax / U>([&](auto ch) {
+                constexpr int p = U * ch();
+                if (p < k) {  // (rows of W past k-1 are finite and meet zeros)
+                    __builtin_amdgcn_sched_barrier(0);
+                    cplx y0[U], y1[U];
+                    each_i<0, U>([&](auto u) {
+                        y0[u()] = w0[p + u()];
+                        y1[u()] = w1[p + u()];
+                    });
+                    each_i<0, U>([&](auto u) {
+                        constexpr int e = u();
+                        if constexpr (e % 2) {
+                            a1 = fmac(vrow[p + e], y0[e], a1);
+                            b1 = fmac(vrow[p + e], y1[e], b1);
+                        } else {
+                            a0 = fmac(vrow[p + e], y0[e], a0);
+                            b0 = fmac(vrow[p + e], y1[e], b0);
+                        }
+                    });
+                }
+            });
+            emit(q, a0 + a1);
+            if (q + 1 < k) emit(q + 1, b0 + b1);
+        }
+    }
+}
 
 __device__ __forceinline__ void solve_eig_body(const SolveArgs& a, EigShared& sh) {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -872,7 +948,11 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a, EigShared& sh
             sh.R[idx] = in ? v : i == jj + 32 && jj < 32 ? 1.0 : 0.0;
         }
     }
-    if (tid < kRMax) sh.sig[tid] = tid < k ? a.sigma[tid] : 1.0;
+    if (tid < kRMax) {
+        const double sg = tid < k ? a.sigma[tid] : 1.0;
+        sh.sig[tid] = sg;
+        sh.isig[tid] = 1.0 / sg;
+    }
     __syncthreads();
     if (wave == 0) {
         int total = 0;
@@ -1138,68 +1218,9 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a, EigShared& sh
         }
     }
     __syncthreads();
-    const int bgq = sh.bg;
-    const cplx fbg = sh.fbg;
-
-    // ---- C = V_r Sigma^-1 W (m x k complex), row-major with row stride 2 r;
-    // thread i keeps row i of V_r Sigma^-1 in registers, W (sorted) is in LDS
-    for (int i = tid; i < m; i += kEigThreads) {
-        // (columns past k-1 read column k-1 and are zeroed: every load in flight at once)
-        cplx vrow[kRMax];
-#pragma unroll
-        for (int p = 0; p < kRMax; ++p) {
-            const int pc = p < k ? p : k - 1;
-            cplx v;
-            if (a.cplx) v = cplx{a.V[2 * (i + (int64_t)pc * ldv)], a.V[2 * (i + (int64_t)pc * ldv) + 1]};
-            else v = mkc(a.V[i + (int64_t)pc * ldv]);
-            vrow[p] = p < k ? v * (1.0 / sh.sig[pc]) : mkc(0.0);
-        }
-        // two columns q at a time: four independent accumulation chains (the
-        // sums of each column keep their order)
-        auto emit = [&](int q, const cplx& acc) {
-            if (q == bgq && a.Bbg) {
-                // background coefficients beta_i = C[i][bg] b_bg lambda_bg^m
-                const cplx bt = acc * fbg;
-                if (a.coef_f64) {
-                    reinterpret_cast<double*>(a.Bbg)[2 * i] = bt.re;
-                    reinterpret_cast<double*>(a.Bbg)[2 * i + 1] = bt.im;
-                } else {
-                    reinterpret_cast<float*>(a.Bbg)[2 * i] = (float)bt.re;
-                    reinterpret_cast<float*>(a.Bbg)[2 * i + 1] = (float)bt.im;
-                }
-            }
-            const int64_t o = (int64_t)i * 2 * a.r + 2 * q;
-            if (a.coef_f64) {
-                double* B = reinterpret_cast<double*>(a.Bphi);
-                B[o] = acc.re;
-                B[o + 1] = acc.im;
-            } else {
-                float* B = reinterpret_cast<float*>(a.Bphi);
-                B[o] = (float)acc.re;
-                B[o + 1] = (float)acc.im;
-            }
-        };
-        for (int q = 0; q < k; q += 2) {
-            const int q1 = q + 1 < k ? q + 1 : q;
-            cplx a0 = mkc(0.0), a1 = mkc(0.0), b0 = mkc(0.0), b1 = mkc(0.0);
-            // (the reads of Y stay under p < k: unconditional, the compiler
-            // hoists them all and the grouped kernel needs more registers
-            // than a retiring projection workgroup frees)
-#pragma unroll
-            for (int p = 0; p < kRMax; p += 2) {
-                if (p < k) {
-                    a0 = a0 + vrow[p] * sh.Y[p + q * LDH];
-                    b0 = b0 + vrow[p] * sh.Y[p + q1 * LDH];
-                }
-                if (p + 1 < k) {
-                    a1 = a1 + vrow[p + 1] * sh.Y[p + 1 + q * LDH];
-                    b1 = b1 + vrow[p + 1] * sh.Y[p + 1 + q1 * LDH];
-                }
-            }
-            emit(q, a0 + a1);
-            if (q + 1 < k) emit(q + 1, b0 + b1);
-        }
-    }
+    // ---- C = V_r Sigma^-1 W (m x k complex), row-major with row stride 2 r
+    if (a.cplx) coef_rows<cplx>(a, sh, m, k);
+    else coef_rows<double>(a, sh, m, k);
     if (tid == 0) {
         st->qr_iters = sh.total;
         if (sh.failed) st->solve_status = ST_E_CONVERGENCE;
