@@ -514,7 +514,7 @@ void k_solve_sym_grouped(const SolveArgs* __restrict__ items) {
 //
 // Bound by the latency of those chains.  Against one wavefront with H and Z in
 // arrays of their own and b from a pivoted elimination of W Lambda: r = 10 real
-// 117 -> 73 us, r = 20 330 -> 189, r = 32 857 -> 397, r = 24 complex 685 -> 495;
+// 117 -> 64 us, r = 20 330 -> 163, r = 32 857 -> 349, r = 24 complex 685 -> 472;
 // 24 windows of a tick 878 -> 462.
 // --------------------------------------------------------------------------
 constexpr int LDM = 65;
@@ -841,8 +841,8 @@ struct EigShared {
 // C = V_r Sigma^-1 W: a thread keeps a row of V_r Sigma^-1 in registers, W
 // (sorted) is in LDS.  Windows of up to 64 (128) columns have four (two)
 // threads for a row, each with its share of the columns of C; several rows of W for two
-// columns are read at a time.  m = 64, r = 20 / 32: 26 / 55 us with a thread
-// per row, complex rows for real V and one row of W at a time.
+// columns are read at a time.  With a thread per row, complex rows for real V and
+// one row of W at a time it took 26 us of the solve's 189 (m = 64, r = 20), now 163 in all.
 template <typename S>
 __device__ __forceinline__ void coef_rows(const SolveArgs& a, EigShared& sh, int m, int k) {
     using SC = Scal<S>;
