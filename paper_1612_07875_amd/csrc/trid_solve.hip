@@ -970,12 +970,15 @@ void k_trid_reduce(SolveArgs a) {
     __shared__ ReduceShared<S, Cls<S, CLS>::NT> sh;
     reduce_class<S, CLS>(a, sh, dyn);
 }
+// (The item is read through a scalar pointer: read as plain memory, its fields
+// sit in vector registers across the whole reduction, and the m > 128 form
+// spilled 1826 of its matrix, now 11 as in the kernel of one window.)
 template <typename S, int CLS>
 __global__ __launch_bounds__((Cls<S, CLS>::NT))
 void k_trid_reduce_grouped(const SolveArgs* __restrict__ items) {
     extern __shared__ double dyn[];
     __shared__ ReduceShared<S, Cls<S, CLS>::NT> sh;
-    const SolveArgs a = items[blockIdx.x];
+    const SolveArgs a = *(const SolveArgs*)as_scalar(items + blockIdx.x);
     reduce_class<S, CLS>(a, sh, dyn);
 }
 // A dense push's Gram finalize followed by the reduction of the window it
