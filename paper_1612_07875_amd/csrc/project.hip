@@ -64,15 +64,17 @@ template <> struct Acc<float> {
     static __device__ __forceinline__ v4f mma(float a, float b, v4f c) {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
+    static __device__ __forceinline__ int row(int g, int v) { return 4 * g + v; }
 };
 template <> struct Acc<double> {
     using type = v4d;
     static __device__ __forceinline__ v4d mma(double a, double b, v4d c) {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
+    static __device__ __forceinline__ int row(int g, int v) { return g + 4 * v; }
 };
 
-constexpr int kOLD = 17;  // padded row length of the BF16x3 form's output stage
+constexpr int kOLD = 17;  // padded row length of the output stage (BF16x3 and short windows)
 constexpr int kStage = kThreads / 64 * 64 * kOLD;
 
 // k-steps (of 4 window columns) whose coefficients a lane reads at once, and
@@ -193,6 +195,11 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int blk, T* c
     // beside this kernel, keep their data cached
     T* out = reinterpret_cast<T*>(a.out);
     const bool wide = ((uintptr_t)out | (uintptr_t)(sizeof(T) * (a.cplx_out ? 2 : 1) * a.ldo)) % 16 == 0;
+    // FP64 modes that outweigh the window and the caches are stored plainly: a
+    // store covers half of each line, the next one the rest, and nontemporal
+    // halves of a full memory queue went out one by one (n = 2^20, m = 16,
+    // r = 16: 150 us, plainly 99; but n = 100,003: 15.3 and 16.8)
+    const bool heavy = F64 && a.cplx_out && 2 * a.kmax >= m && a.n * a.kmax > (int64_t)1 << 23;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
@@ -207,7 +214,10 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int blk, T* c
                     if (c >= kcols) continue;
                     T* o = out + 2 * (row + (int64_t)(c >> 1) * a.ldo);
                     if (wide && r1) {
-                        if constexpr (F64) {
+                        if (F64 && heavy) {
+                            *reinterpret_cast<t2*>(o) = t2{p[v], p[v + 1]};
+                            *reinterpret_cast<t2*>(o + 2) = t2{q[v], q[v + 1]};
+                        } else if constexpr (F64) {
                             __builtin_nontemporal_store(t2{p[v], p[v + 1]}, reinterpret_cast<t2*>(o));
                             __builtin_nontemporal_store(t2{q[v], q[v + 1]}, reinterpret_cast<t2*>(o + 2));
                         } else {
@@ -239,6 +249,135 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int blk, T* c
                 }
             }
         }
+    }
+}
+
+// The product of a short window (the same sums, bit for bit): every wavefront
+// takes its coefficients straight from memory, a group of k-steps ahead of the
+// products as the window's columns, and the output tiles go through LDS so
+// that a store writes 64 consecutive rows of a column.  No barrier, and no
+// column is read twice; the form above waits for its coefficients and reads
+// two groups past the window, which a longer window hides.
+//
+// Where it is faster (us, this form and the one above, n = 2^20 unless named):
+// FP32, one column tile, m = 8, r = 2: 17 and 26, m = 24, r = 6: 38 and 41,
+// m = 40, r = 8 level, m = 64, r = 8: 77 and 77; two tiles, m = 12: 0.92, m = 16,
+// r = 16: 57 and 54; up to n = 131,072, where every workgroup runs at once, m <= 48
+// and up to three tiles (1 of 11 to 15 us).  FP64 data, one tile: m = 16, r = 8: 62 and
+// 80, m = 64: 143 and 158, m = 128: 250 and 265, m = 256 level; for n = 100,003
+// only to m = 32.  FP32 data in FP64 never (24 and 24 at m = 3; 62 and 54 at m = 8).
+template <typename TX, typename T> __host__ __device__ inline bool project_direct(int m, int nt, int64_t n) {
+    if constexpr (sizeof(TX) == 8) return nt == 1 && (m <= 32 || (m <= 128 && n > 200000));
+    else if constexpr (sizeof(T) == 8) return false;
+    else return (nt == 1 && m <= 40) || (nt == 2 && m <= 12) || (nt <= 3 && m <= 48 && n <= 131072);
+}
+template <typename TX, typename T, int NT>
+__device__ __forceinline__ void project_body_direct(const ProjectArgs& a, int blk, T* stage) {
+    using AccT = typename Acc<T>::type;
+    constexpr int KG = sizeof(T) == 8 ? 2 : 4;  // k-steps (of 4 columns) per group
+    constexpr int OLD = kOLD;
+    const DevState* st = a.st;
+    if (st->solve_status == ST_E_NOT_READY) return;
+    if (a.block_only && st->block_rejected) return;
+    const int k_eff = st->r_eff;
+    const int kcols = a.cplx_out ? 2 * k_eff : k_eff;
+    if (kcols == 0) return;
+    const int m = window_cols(a.m, a.buildup, st);  // columns of X_sub (fewer during a build-up start)
+    const int rowstride = a.cplx_out ? 2 * a.kmax : a.kmax;
+    const T* B = reinterpret_cast<const T*>(a.B);
+
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    const int64_t row0 = (int64_t)blk * kRowsPerBlock + wave * kRowsPerWave;
+    const int oldest = st->oldest;
+    const TX* ring = reinterpret_cast<const TX*>(a.ring);
+
+    AccT acc[4][NT];
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[rt][nt] = AccT{0, 0, 0, 0};
+
+    bool rin[4];
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt) rin[rt] = row0 + 16 * rt + li < a.n;
+
+    T av[2][KG][4], bv[2][KG][NT];
+    auto load_group = [&](int buf, int k0) {
+#pragma unroll
+        for (int g = 0; g < KG; ++g) {
+            const int col = k0 + 4 * g + lk;
+            const bool cin = col < m;
+            const TX* cp = ring + (int64_t)slot_of(oldest, a.first + (cin ? col : 0), a.slots) * a.ld;
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt)
+                av[buf][g][rt] = (cin && rin[rt]) ? (T)__builtin_nontemporal_load(&cp[row0 + 16 * rt + li]) : T(0);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const int c = 16 * nt + li;
+                bv[buf][g][nt] = (cin && c < kcols) ? B[(int64_t)col * rowstride + c] : T(0);
+            }
+        }
+    };
+    auto mma_group = [&](int buf) {
+#pragma unroll
+        for (int g = 0; g < KG; ++g)
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    acc[rt][nt] = Acc<T>::mma(av[buf][g][rt], bv[buf][g][nt], acc[rt][nt]);
+    };
+    // two groups per iteration so that both register buffers have static indices
+    const int ngroups = (m + 4 * KG - 1) / (4 * KG);
+    load_group(0, 0);
+    for (int gi = 0; gi < ngroups; gi += 2) {
+        if (gi + 1 < ngroups) load_group(1, (gi + 1) * 4 * KG);
+        mma_group(0);
+        if (gi + 1 >= ngroups) break;
+        if (gi + 2 < ngroups) load_group(0, (gi + 2) * 4 * KG);
+        mma_group(1);
+    }
+
+    // window columns are read and modes written nontemporally: each is
+    // touched once per call, and the solves of the next push, which may run
+    // beside this kernel, keep their data cached
+    T* out = reinterpret_cast<T*>(a.out);
+    T* sw = stage + wave * 64 * OLD;
+    const int64_t row = row0 + lane;  // the row this lane stores
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        if (16 * nt >= kcols) break;
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sw[(16 * rt + Acc<T>::row(lk, v)) * OLD + li] = acc[rt][nt][v];
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (row < a.n) {
+            if (a.cplx_out) {
+#pragma unroll
+                for (int cc = 0; cc < 16; cc += 2) {
+                    const int c = 16 * nt + cc;
+                    if (c < kcols) {
+                        const int64_t o = 2 * (row + (int64_t)(c >> 1) * a.ldo);
+                        __builtin_nontemporal_store(sw[lane * OLD + cc], &out[o]);
+                        __builtin_nontemporal_store(sw[lane * OLD + cc + 1], &out[o + 1]);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int cc = 0; cc < 16; ++cc) {
+                    const int c = 16 * nt + cc;
+                    if (c < kcols) out[row + (int64_t)c * a.ldo] = sw[lane * OLD + cc];
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
 }
 
@@ -349,12 +488,23 @@ void k_project_mfma(ProjectArgs a) {
     project_body<TX, T, NT>(a, blockIdx.x, reinterpret_cast<T*>(pdyn));
 }
 
+template <typename TX, typename T, int NT>
+__global__ __launch_bounds__(kThreads)
+void k_project_direct(ProjectArgs a) {
+    __shared__ T stage[kStage];
+    project_body_direct<TX, T, NT>(a, blockIdx.x, stage);
+}
+
 template <int NT>
 __global__ __launch_bounds__(kThreads)
 void k_project_bf3(ProjectArgs a) {
     __shared__ float stage[kStage];
     project_body_bf3<NT>(a, blockIdx.x, stage);
 }
+
+// Items of a grouped launch that take the direct form: one column tile (two
+// would need more registers than the kernel has for three workgroups a CU).
+__host__ __device__ inline bool grouped_direct(int m, int nt) { return nt == 1 && m <= 40; }
 
 // Grouped form over many streams (FP32 ring and coefficients; each item in
 // FP32 or BF16x3 by its precision): block b belongs to item i with
@@ -379,7 +529,10 @@ void k_project_grouped(const ProjectArgs* __restrict__ items, const int* __restr
         return;
     }
     switch (nt) {
-        case 1: project_body<float, float, 1>(a, blk, lds); break;
+        case 1:
+            if (grouped_direct(a.m, nt)) project_body_direct<float, float, 1>(a, blk, lds);
+            else project_body<float, float, 1>(a, blk, lds);
+            break;
         case 2: project_body<float, float, 2>(a, blk, lds); break;
         case 3: project_body<float, float, 3>(a, blk, lds); break;
         default: project_body<float, float, 4>(a, blk, lds); break;
@@ -389,11 +542,19 @@ void k_project_grouped(const ProjectArgs* __restrict__ items, const int* __restr
 template <typename TX, typename T, int NT>
 hipError_t launch_nt(const ProjectArgs& a, hipStream_t s) {
     const unsigned gx = (unsigned)((a.n + kRowsPerBlock - 1) / kRowsPerBlock);
+    if constexpr (sizeof(TX) == sizeof(T) && NT <= (sizeof(T) == 8 ? 1 : 3)) {
+        if (project_direct<TX, T>(a.m, NT, a.n)) {
+            hipLaunchKernelGGL((k_project_direct<TX, T, NT>), dim3(gx), dim3(kThreads), 0, s, a);
+            return hipGetLastError();
+        }
+    }
     const size_t lds = project_lds<T>(a.m, NT);
     auto kern = k_project_mfma<TX, T, NT>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    if (lds > 65536) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)project_lds<T>(kMaxM, NT));
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(kern, dim3(gx), dim3(kThreads), lds, s, a);
     return hipGetLastError();
 }
@@ -1797,15 +1958,14 @@ int project_item_blocks(int64_t n) { return (int)((n + kRowsPerBlock - 1) / kRow
 
 // LDS of one item of a grouped launch.
 size_t project_item_lds(const ProjectArgs& a) {
-    if (a.precision == 2 /* DMD_PREC_BF16X3 */) return sizeof(float) * kStage;
-    return project_lds<float>(a.m, ((a.cplx_out ? 2 * a.kmax : a.kmax) + 15) / 16);
+    const int nt = ((a.cplx_out ? 2 * a.kmax : a.kmax) + 15) / 16;
+    if (a.precision == 2 /* DMD_PREC_BF16X3 */ || grouped_direct(a.m, nt)) return sizeof(float) * kStage;
+    return project_lds<float>(a.m, nt);
 }
 
 hipError_t launch_project_grouped(const ProjectArgs* items, const int* blk_start, int nitems, int total_blocks,
                                   size_t lds, hipStream_t s) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_project_grouped),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    // (lds <= 64 KB: FP32 coefficients of 256 columns in four tiles)
     hipLaunchKernelGGL(k_project_grouped, dim3(total_blocks), dim3(kThreads), lds, s, items, blk_start, nitems);
     return hipGetLastError();
 }
