@@ -1778,7 +1778,7 @@ struct dmd_batch {
     uint64_t uses = 0;
     hipStream_t cap_stream = nullptr;  // capture stream (default priority)
     hipStream_t side = nullptr;        // the wide windows' chain of a tick (default priority)
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    hipEvent_t ev_fork = nullptr, ev_frames = nullptr, ev_join = nullptr;
     std::vector<std::shared_ptr<SharedEvent>> events;  // at most one per member, and one
     int64_t budget = 0, used = 0;
     std::vector<dmd_stream*> members;
@@ -1809,6 +1809,7 @@ static void batch_free(dmd_batch* b) {
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
     if (b->side) (void)hipStreamDestroy(b->side);
     if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
+    if (b->ev_frames) (void)hipEventDestroy(b->ev_frames);
     if (b->ev_join) (void)hipEventDestroy(b->ev_join);
     for (int i = 0; i < 2; ++i) {
         if (b->host[i]) (void)hipHostFree(b->host[i]);
@@ -1860,6 +1861,7 @@ DMD_API int dmd_batch_create(const dmd_batch_opts_t* opts, dmd_batch_t** out) {
     if (e == hipSuccess && b->graphs > 0) e = hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_frames, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev_join, hipEventDisableTiming);
     if (e != hipSuccess) {
         batch_free(b);
@@ -1982,7 +1984,9 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
     // behind their Gram pass on the tick's stream.  The solves keep a workgroup
     // per window busy and leave the memory idle: a wide window's
     // (reduction, values, vectors and eig in turn, about 700 us at m = 128, r =
-    // 32) run beside the other members' Gram pass and solves.  One chain where
+    // 32) run beside the other members' Gram pass and solves; its projection
+    // waits for that Gram pass (no modes are written before every frame is
+    // read).  One chain where
     // the members are all of one kind, or where one runs kernels of its own
     // (its solve is in the same tables).  24 unlike windows (m = 16 .. 128):
     // 3501 us in one chain, 3143 in two (both with two events per member recorded behind the tick).
@@ -2111,21 +2115,31 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
         e = phase("batch_gram", [&] {
             hipError_t f = hipSuccess;
             if (fork) {
-                const int rest[3] = {0, nt[1], nt[2]};
                 f = chain_gram(1);
                 if (f == hipSuccess) f = hipEventRecord(b->ev_fork, q);
-                if (f == hipSuccess) f = hipStreamWaitEvent(b->side, b->ev_fork, 0);
-                if (f == hipSuccess) f = dmd::launch_trid_grouped(rl, rest, b->side);
-                if (f == hipSuccess) f = chain_eig(1, b->side);
-                if (f == hipSuccess) f = chain_project(1, b->side);
-                // (joined below on every path: a capture must not end with the side stream in it)
-                const hipError_t r = hipEventRecord(b->ev_join, b->side);
-                if (f == hipSuccess) f = r;
             }
             if (f == hipSuccess) f = chain_gram(0);
             for (size_t u = 0; u < own.size() && f == hipSuccess; ++u) f = own_gram(q, own[u]);
+            // (a frame may lie in another member's modes of the tick before:
+            // the side chain writes its modes behind every Gram pass)
+            if (fork && ch[1].np > 0 && f == hipSuccess) f = hipEventRecord(b->ev_frames, q);
             return f;
         });
+        bool forked = false;
+        if (fork && e == hipSuccess) {
+            const int rest[3] = {0, nt[1], nt[2]};
+            e = hipStreamWaitEvent(b->side, b->ev_fork, 0);
+            forked = e == hipSuccess;
+            if (e == hipSuccess) e = dmd::launch_trid_grouped(rl, rest, b->side);
+            if (e == hipSuccess) e = chain_eig(1, b->side);
+            if (e == hipSuccess && ch[1].np > 0) {
+                e = hipStreamWaitEvent(b->side, b->ev_frames, 0);
+                if (e == hipSuccess) e = chain_project(1, b->side);
+            }
+            // (joined below on every path: a capture must not end with the side stream in it)
+            const hipError_t f = hipEventRecord(b->ev_join, b->side);
+            if (e == hipSuccess) e = f;
+        }
         if (e == hipSuccess)
             e = phase("batch_solve", [&] {
                 hipError_t f = dmd::launch_jacobi_grouped(reinterpret_cast<const dmd::SolveArgs*>(D + b->L.lds), nl,
@@ -2141,7 +2155,7 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
                 for (size_t u = 0; u < own.size() && f == hipSuccess; ++u) f = own_project(q, own[u]);
                 return f;
             });
-        if (fork) {
+        if (forked) {
             const hipError_t f = hipStreamWaitEvent(q, b->ev_join, 0);
             if (e == hipSuccess) e = f;
         }
