@@ -601,8 +601,10 @@ int dmd_batch_info(dmd_batch_t* b, int32_t* nstreams, int64_t* used_bytes,
  * ingest's two DFT kernels); for block pushes "gram_block" (block Gram pass,
  * reduction and commit), "block_solve" (all windows' solves), "pack_block"
  * (packing the projection inputs) and "project_block" (all windows' modes);
- * for batch ticks "batch_gram", "batch_solve", "batch_project" (eager ticks)
- * or "batch_graph" (graph ticks).
+ * for batch ticks "batch_gram", "batch_solve", "batch_project" (eager ticks;
+ * dense FP32 members with m <= 64 and m > 64 in one tick run in two chains,
+ * whose solves and projections are a launch each and overlap in time) or
+ * "batch_graph" (graph ticks).
  * dmd_profile_read waits for the recorded events and returns the number of
  * launches of `kernel` and their summed duration in milliseconds since the
  * last dmd_profile_reset. */

@@ -2104,7 +2104,7 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
     auto enqueue = [&](hipStream_t q, bool time_phases) -> hipError_t {
         hipError_t e = hipMemcpyAsync(D, H, b->L.bytes, hipMemcpyHostToDevice, q);
         if (e != hipSuccess) return e;
-        auto phase = [&](const char* name, auto&& fn) { return time_phases ? timed(name, q, fn) : fn(); };
+        auto phase = [&](const char* name, hipStream_t t, auto&& fn) { return time_phases ? timed(name, t, fn) : fn(); };
         auto chain_gram = [&](int c) -> hipError_t {
             const int at = c == 0 ? ch[1].na : 0;
             if (ch[c].na == 0) return hipSuccess;
@@ -2128,7 +2128,7 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
             cl[c] = reinterpret_cast<const dmd::SolveArgs*>(D + b->L.ctrid[c]);
         }
         const int narrow[3] = {nt[0], fork ? 0 : nt[1], fork ? 0 : nt[2]};
-        e = phase("batch_gram", [&] {
+        e = phase("batch_gram", q, [&] {
             hipError_t f = hipSuccess;
             if (fork) {
                 f = chain_gram(1);
@@ -2146,18 +2146,21 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
             const int rest[3] = {0, nt[1], nt[2]};
             e = hipStreamWaitEvent(b->side, b->ev_fork, 0);
             forked = e == hipSuccess;
-            if (e == hipSuccess) e = dmd::launch_trid_grouped(rl, rest, b->side);
-            if (e == hipSuccess) e = chain_eig(1, b->side);
+            if (e == hipSuccess)
+                e = phase("batch_solve", b->side, [&] {
+                    const hipError_t f = dmd::launch_trid_grouped(rl, rest, b->side);
+                    return f == hipSuccess ? chain_eig(1, b->side) : f;
+                });
             if (e == hipSuccess && ch[1].np > 0) {
                 e = hipStreamWaitEvent(b->side, b->ev_frames, 0);
-                if (e == hipSuccess) e = chain_project(1, b->side);
+                if (e == hipSuccess) e = phase("batch_project", b->side, [&] { return chain_project(1, b->side); });
             }
             // (joined below on every path: a capture must not end with the side stream in it)
             const hipError_t f = hipEventRecord(b->ev_join, b->side);
             if (e == hipSuccess) e = f;
         }
         if (e == hipSuccess)
-            e = phase("batch_solve", [&] {
+            e = phase("batch_solve", q, [&] {
                 hipError_t f = dmd::launch_jacobi_grouped(reinterpret_cast<const dmd::SolveArgs*>(D + b->L.lds), nl,
                                                           reinterpret_cast<const dmd::SolveArgs*>(D + b->L.glb), ng, q);
                 if (f == hipSuccess) f = dmd::launch_trid_grouped(rl, narrow, q);
@@ -2166,7 +2169,7 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
                 return f;
             });
         if (e == hipSuccess && modes)
-            e = phase("batch_project", [&] {
+            e = phase("batch_project", q, [&] {
                 hipError_t f = chain_project(0, q);
                 for (size_t u = 0; u < own.size() && f == hipSuccess; ++u) f = own_project(q, own[u]);
                 return f;
