@@ -624,7 +624,7 @@ __device__ __forceinline__ int deflate(S* M, int hi, int lane, double hmax) {
 // complex-conjugate pair converges together in real arithmetic.
 //
 // A step is one chain: the reflector from (x, y, z) (in registers: u =
-// (x + sign(x) s, y, z), s = ||(x, y, z)||, tau = 1 / (s (s + |x|)), by the
+// (x + sign(x) s, y, z), s = ||(x, y, z)||, tau = 2 / u^T u, by the
 // hardware estimates plus Newton steps), the three rows (lane = column), LDS,
 // the three columns (lane = row of H or Z), and the next (x, y, z) from the
 // lanes that hold them.  22 sweeps of a 20 x 20 matrix take 68 us, deflation
@@ -678,13 +678,13 @@ __device__ __forceinline__ void real_schur(double* M, int k, int lane, int max_i
             double* row = M + j * LDM + kk;     // rows kk .. kk+2 of column j
             double* col = M + kk * LDM + lane;  // columns kk .. kk+2 of row `lane`
             const double r0 = row[0], r1 = row[1], r2 = row[2];
-            const double s2 = fma(x, x, fma(y, y, z * z));
+            const double yz2 = fma(y, y, z * z), s2 = fma(x, x, yz2);
             const bool none = !(s2 > 1e-300);   // (nothing to annihilate: z and y are zero, or vanish beside H)
-            const double inv = rsqrt_acc(s2);
-            const double nrm = s2 * inv, ax = fabs(x);
-            const double u0 = none ? 0.0 : x + copysign(nrm, x);
-            const double tau = none ? 0.0 : inv * rcp_acc(nrm + ax);
-            const double f = tau * fma(u0, r0, fma(y, r1, z * r2));
+            const double u = x + copysign(s2 * rsqrt_acc(s2), x), u0 = none ? 0.0 : u;
+            // (tau = 2 / u^T u from u itself and not from the norms: I - tau u u^T is
+            // then orthogonal to the rounding of tau alone)
+            const double half_tau = none ? 0.0 : rcp_acc(fma(u, u, yz2)), tau = 2.0 * half_tau;
+            const double ru = fma(u0, r0, fma(y, r1, z * r2)), f = half_tau * (ru + ru);
             // the entries below the subdiagonal of column kk-1 become zero
             const bool below = kk > l && j == kk - 1;
             const double n0 = fma(-f, u0, r0), n1 = fma(-f, y, r1), n2 = fma(-f, z, r2);
