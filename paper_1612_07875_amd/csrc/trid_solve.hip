@@ -239,7 +239,8 @@ struct Reducer {
         S* y = sh.y[j & 1];
         const int dj = j + 1;
         // the reflector of column j: beta = -sign(Re alpha) ||x||, z = alpha - beta,
-        // tau = 1 / (||x||^2 + |alpha| ||x||) (complex: -1 / (beta conj(z)))
+        // tau = 2 / u^T u, from u itself so that the rounding of beta does not
+        // cost orthogonality (complex: -1 / (beta conj(z)))
         const S alpha = x[dj];
         S uk[kKeep ? NB : 1], ur[NA];
         double s2 = 0.0;
@@ -252,12 +253,14 @@ struct Reducer {
         s2 = row_sum(s2);
         const bool flat = !(s2 > 1e-200);  // (nothing, beside a largest diagonal entry near 1)
         const double inv = rsqrt_acc(s2), ar = SC::re(alpha);
-        const double nrm = flat ? 0.0 : s2 * inv;
+        double nrm = s2 * inv;
+        if constexpr (sizeof(S) == sizeof(cplx)) nrm = fma(0.5 * inv, fma(-nrm, nrm, s2), nrm);  // (tau is taken from it)
+        nrm = flat ? 0.0 : nrm;
         const double beta = -copysign(nrm, ar);
         const S z = alpha - SC::fromc(mkc(beta));
         S tau;
-        if constexpr (sizeof(S) == sizeof(cplx)) tau = (rcp_acc(norm2(z)) * copysign(inv, ar)) * z;
-        else tau = inv * rcp_acc(nrm + fabs(ar));
+        if constexpr (sizeof(S) == sizeof(cplx)) tau = copysign(rcp_acc(nrm * norm2(z)), ar) * z;
+        else tau = 2.0 * rcp_acc(fma(z, z, fma(-ar, ar, s2)));
         tau = sel(flat, SC::zero(), tau);
         // (every thread writes the same values)
         sh.e[j] = beta;
@@ -424,7 +427,7 @@ __device__ __forceinline__ void reduce_body(const SolveArgs& a, ReduceShared<S, 
 
 // --------------------------------------------------------------------------
 // k_trid_values: eigenvalue k of T / scale by one wavefront.  64 equally
-// spaced points of its bracket per round give 6 bits, so nine rounds of n
+// spaced points of its bracket per round give 6 bits, so ten rounds of n
 // steps replace the 34 (m = 128) of the two lanes per eigenvalue that one
 // workgroup has: the Sturm counts are the solve's largest arithmetic, and
 // the eigenvalues are independent, so they go to as many CUs as there are
@@ -476,12 +479,16 @@ template <typename S> __device__ __forceinline__ void values_body(const SolveArg
     const int k = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (k >= n) return;
     const int lane = threadIdx.x & 63, npad = trid_padded(n);
-    // (off centre, so that the eigenvalues below the counts' resolution come out
-    // as 3.9e-17, of the size of that resolution, and not as an exact zero)
+    // (off centre, so that an eigenvalue of zero comes out as 1e-19 and not as an
+    // exact zero)
     double lo = -1.0 - 8.0 * kEps, hi = 1.0 + 4.0 * kEps;
     SturmRow row = sturm_load(de, 1);
     constexpr double part = 1.0 / 65.0;
-    for (int it = 0; it < 9; ++it) {  // 2 / 65^9 < eps / 2
+    // Ten rounds, 2 / 65^10 = 1.5e-18: the counts of a graded T resolve its small
+    // eigenvalues far below eps ||T||, and the vectors of neighbours among them
+    // are as orthogonal as their difference is exact (after nine rounds, 9.7e-17,
+    // V^T V was off by 3e-14 at m = 32, r = 10 where ten leave 6e-15)
+    for (int it = 0; it < 10; ++it) {
         const double wd = hi - lo;
         const double x = fma(wd, (double)(lane + 1) * part, lo);
         const uint64_t mask = __ballot(sturm_count64(de, npad, x, row) > k);
