@@ -184,7 +184,8 @@ hipError_t launch_jacobi_grouped(const SolveArgs* items_lds, int n_lds, const So
 // The tridiagonal solves come in three size classes (trid_class), each with a
 // list of its own: items[c] holds count[c] windows of class c.
 int trid_class(int m, int cplx);
-hipError_t launch_trid_grouped(const SolveArgs* const items[3], const int count[3], hipStream_t s);
+// m_small: no window of class 0 has more columns.
+hipError_t launch_trid_grouped(const SolveArgs* const items[3], const int count[3], hipStream_t s, int m_small = 64);
 // Grouped Hermitian (complex) tridiagonal solves.
 hipError_t launch_trid_grouped_cplx(const SolveArgs* const items[3], const int count[3], hipStream_t s);
 // Hermitian windows of more than 128 columns, one workgroup each (matrix in

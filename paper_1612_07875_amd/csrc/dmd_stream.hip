@@ -981,7 +981,7 @@ DMD_API int dmd_stream_push_block(dmd_stream_t* h, const void* X_new, int64_t ld
         int count[3] = {0, 0, 0};
         count[dmd::trid_class(h->m, 0)] = k;
         HIP_TRY(timed("block_solve", s, [&] {
-            hipError_t e = h->use_trid ? dmd::launch_trid_grouped(lists, count, s)
+            hipError_t e = h->use_trid ? dmd::launch_trid_grouped(lists, count, s, h->m)
                                        : dmd::launch_jacobi_grouped(t, lds ? k : 0, t, lds ? 0 : k, s);
             return e != hipSuccess ? e : dmd::launch_eig_grouped(t, k, s);
         }));

@@ -3,7 +3,8 @@
 //
 //   k_trid_reduce   one workgroup: Householder reduction T = Q^* xtx Q with the
 //                   matrix in registers
-//   k_trid_values   one wavefront per eigenvalue: multisection of T
+//   k_trid_values   one wavefront per eigenvalue: multisection of T (windows of
+//                   up to 8 columns: in the third kernel)
 //   k_trid_vectors  one workgroup: the r leading eigenvectors (twisted
 //                   factorizations, back-transformation), V_r, the A~ of
 //                   Algorithm 2 and the POD coefficients
@@ -472,12 +473,8 @@ __device__ __forceinline__ int sturm_count64(scalar_ptr<double> de, int npad, do
     return cnt;
 }
 
-template <typename S> __device__ __forceinline__ void values_body(const SolveArgs& a) {
-    const TridWork<S> w(a);
-    const int n = (int)as_scalar(w.hdr)[0];
-    const auto de = as_scalar(reinterpret_cast<const double*>(w.de));
-    const int k = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (k >= n) return;
+// eigenvalue k of T / scale (n x n), the same in every lane
+__device__ __forceinline__ double multisect(scalar_ptr<double> de, int n, int k) {
     const int lane = threadIdx.x & 63, npad = trid_padded(n);
     // (off centre, so that an eigenvalue of zero comes out as 1e-19 and not as an
     // exact zero)
@@ -496,7 +493,22 @@ template <typename S> __device__ __forceinline__ void values_body(const SolveArg
         hi = f == 64 ? hi : fma(wd, (double)(f + 1) * part, lo);
         lo = f == 0 ? lo : fma(wd, (double)f * part, lo);
     }
-    if (lane == 0) w.lam[k] = 0.5 * (lo + hi);
+    return 0.5 * (lo + hi);
+}
+
+// Windows of so few columns have a wavefront of k_trid_vectors find each
+// eigenvalue: without the launch of k_trid_values a push and its modes take 50
+// us for 52 at m = 2, r = 1.
+constexpr int kInlineValues = 8;
+
+template <typename S> __device__ __forceinline__ void values_body(const SolveArgs& a) {
+    const TridWork<S> w(a);
+    const int n = (int)as_scalar(w.hdr)[0];
+    const auto de = as_scalar(reinterpret_cast<const double*>(w.de));
+    const int k = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (k >= n || a.m <= kInlineValues) return;
+    const double l = multisect(de, n, k);
+    if ((threadIdx.x & 63) == 0) w.lam[k] = l;
 }
 
 // --------------------------------------------------------------------------
@@ -617,8 +629,13 @@ __device__ __forceinline__ void vectors_body(const SolveArgs& a, VecShared<S>& s
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const double scale = as_scalar(w.hdr)[1];
     const int nv = a.r < n ? a.r : n;
+    const bool inl = NE == 2 && a.m <= kInlineValues;  // (NE = 2: windows of up to 32 columns)
+    if (inl && wave < n) {
+        const double l = multisect(as_scalar(reinterpret_cast<const double*>(w.de)), n, wave);
+        if (lane == 0) sh.lam[wave] = l;
+    }
     for (int i = tid; i < n; i += kVecThreads) {
-        sh.lam[i] = w.lam[i];
+        if (!inl) sh.lam[i] = w.lam[i];
         sh.d[i] = w.de[i].x;
         sh.e[i] = w.e[i];
         if (i + 1 < n) sh.tau[i] = w.tau[i];
@@ -1053,9 +1070,11 @@ inline size_t reduce_lds(int m) { return m > 192 ? sizeof(double) * 8 * 4 * 512 
 
 // values and vectors of one window
 template <typename S, int CLS> hipError_t launch_rest(const SolveArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(k_trid_values<S>, dim3((a.m + 3) / 4), dim3(256), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    if (a.m > kInlineValues) {
+        hipLaunchKernelGGL(k_trid_values<S>, dim3((a.m + 3) / 4), dim3(256), 0, s, a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     const size_t lds = vec_lds<S>(a.m, a.r < a.m ? a.r : a.m);
     if ((e = set_lds(k_trid_vectors<S, CLS>, lds)) != hipSuccess) return e;
     hipLaunchKernelGGL((k_trid_vectors<S, CLS>), dim3(1), dim3(kVecThreads), lds, s, a);
@@ -1085,8 +1104,10 @@ template <typename S, int CLS> hipError_t launch_group(const SolveArgs* items, i
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_trid_reduce_grouped<S, CLS>), dim3(n), dim3(Cls<S, CLS>::NT), lds, s, items);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_trid_values_grouped<S>, dim3((mmax + 3) / 4, n), dim3(256), 0, s, items);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (mmax > kInlineValues) {
+        hipLaunchKernelGGL(k_trid_values_grouped<S>, dim3((mmax + 3) / 4, n), dim3(256), 0, s, items);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     hipLaunchKernelGGL((k_trid_vectors_grouped<S, CLS>), dim3(n), dim3(kVecThreads), vlds, s, items);
     return hipGetLastError();
 }
@@ -1117,10 +1138,10 @@ hipError_t launch_finalize_solve_trid(double* G, const double* partials, int nbl
 
 int trid_class(int m, int cplx) { return cplx ? (m <= 32 ? 0 : m <= 128 ? 1 : 2) : (m <= 64 ? 0 : m <= 128 ? 1 : 2); }
 
-hipError_t launch_trid_grouped(const SolveArgs* const items[3], const int count[3], hipStream_t s) {
+hipError_t launch_trid_grouped(const SolveArgs* const items[3], const int count[3], hipStream_t s, int m_small) {
     hipError_t e = launch_group<double, kClassX>(items[2], count[2], kMaxM, s);
     if (e == hipSuccess) e = launch_group<double, kClassL>(items[1], count[1], 128, s);
-    if (e == hipSuccess) e = launch_group<double, kClassS>(items[0], count[0], 64, s);
+    if (e == hipSuccess) e = launch_group<double, kClassS>(items[0], count[0], m_small, s);
     return e;
 }
 
