@@ -405,10 +405,20 @@ __device__ __forceinline__ void reduce_body(const SolveArgs& a, ReduceShared<S, 
     // the reflectors' stores have landed before their entries j + 1 are replaced
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
-    // T / scale, scale = the largest Gershgorin radius
+    // T / scale, scale = the largest Gershgorin radius; a Gram that is not finite
+    // (a loaded window; pushes reject such snapshots) leaves a T that is not, and
+    // is solved as zero: rank 0
     g = 0.0;
-    for (int i = tid; i < n; i += NT) g = fmax(g, fabs(sh.d[i]) + (i > 0 ? fabs(sh.e[i - 1]) : 0.0) + fabs(sh.e[i]));
-    const double scale = block_max(g);
+    for (int i = tid; i < n; i += NT) {
+        const double rad = fabs(sh.d[i]) + (i > 0 ? fabs(sh.e[i - 1]) : 0.0) + fabs(sh.e[i]);
+        g = rad <= DBL_MAX ? fmax(g, rad) : (double)INFINITY;
+    }
+    double scale = block_max(g);
+    if (!(scale <= DBL_MAX)) {
+        for (int i = tid; i < n; i += NT) sh.d[i] = sh.e[i] = 0.0;
+        scale = 0.0;
+        lds_barrier();
+    }
     const double inv = scale > 0.0 ? 1.0 / scale : 0.0;
     for (int i = tid; i < n; i += NT) {
         const double e0 = i > 0 ? sh.e[i - 1] * inv : 0.0;
