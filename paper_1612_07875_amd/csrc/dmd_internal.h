@@ -29,7 +29,8 @@ struct DevState {
     int32_t qr_iters;           // Hessenberg-QR iterations of the latest solve
     int32_t solves;             // solves run on a full window
     int32_t pushes;             // accepted pushes
-    int32_t vprev_valid;        // Vfull holds the eigenvectors of a converged solve
+    int32_t vprev_valid;        // the latest solve converged with every eigenvector of a full window
+                                // (Jacobi keeps them in Vfull)
     int32_t vprev_push;         // value of `pushes` at that solve
     int32_t warm;               // latest solve was warm-started (1: shifted, 2: same window)
     int32_t skipped;            // latest solve found nothing new and kept the previous results
@@ -148,7 +149,7 @@ struct SolveArgs {
     double* At;            // r x r (complex: interleaved)
     double* W;             // r x r complex
     double* work;          // global scratch: solve_work_doubles (Jacobi: A, V, Q; tridiagonal: T, reflectors)
-    double* Vfull;         // m x m eigenvectors of the latest solve, sigma order
+    double* Vfull;         // Jacobi: m x m eigenvectors of the latest solve, sigma order (else null)
     void* Bphi;            // m x 2r coefficients of Phi (row-major, data precision)
     void* Bpod;            // m x r (real) or m x 2r (complex) coefficients of U
     void* Bbg;             // m complex coefficients of the background (may be null)
@@ -174,7 +175,8 @@ hipError_t launch_solve_sym(const SolveArgs& a, hipStream_t s);
 // factorizations (no warm start).
 hipError_t launch_solve_trid(const SolveArgs& a, hipStream_t s);
 // The finalize of a dense push's Gram pass (launch_gram_finalize) and the
-// real tridiagonal solve of the new window as one launch.
+// real tridiagonal solve of the new window, its reduction in the finalize's
+// launch (m <= 128).
 hipError_t launch_finalize_solve_trid(double* G, const double* partials, int nblk, const SolveArgs& a,
                                       hipStream_t s);
 // Grouped real symmetric solves by Jacobi (one workgroup per item; lds:

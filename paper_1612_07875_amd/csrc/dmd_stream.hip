@@ -434,7 +434,7 @@ void fill_shadow_args(const dmd_stream* h, dmd::SolveArgs& a, int e) {
     a.At = h->sh_At + e * z.At;
     a.W = h->sh_W + e * z.W;
     a.work = h->sh_work + e * z.work;
-    a.Vfull = h->sh_Vfull + e * z.Vfull;
+    a.Vfull = h->sh_Vfull ? h->sh_Vfull + e * z.Vfull : nullptr;
     a.Bphi = static_cast<char*>(h->sh_Bphi) + e * z.Bphi;
     a.Bpod = static_cast<char*>(h->sh_Bpod) + e * z.Bpod;
     a.res_block = res;
@@ -635,8 +635,10 @@ int create_impl(int64_t n, int32_t m, int32_t r, const dmd_opts_t* opts, dmd_str
     const int cw = h->cplx ? 2 : 1;
     h->nblk_cap = dmd::gram_push_blocks(n, h->elem_bytes);
     const size_t coef = h->coef_f64 ? 8 : 4;
-#define ALLOC(p, bytes)                                  \
-    if (rc == DMD_OK) rc = dev_alloc(h, &(p), (bytes));
+#define ALLOC(p, bytes)                                      \
+    do {                                                     \
+        if (rc == DMD_OK) rc = dev_alloc(h, &(p), (bytes));  \
+    } while (0)
     if (h->cplx) {
         h->max_nnz = o.max_nnz;
         h->nblk_cap = dmd::csr_partials_per_column();
@@ -668,7 +670,7 @@ int create_impl(int64_t n, int32_t m, int32_t r, const dmd_opts_t* opts, dmd_str
     ALLOC(h->At, sizeof(double) * cw * (size_t)r * r);
     ALLOC(h->W, sizeof(double) * 2 * (size_t)r * r);
     ALLOC(h->work, sizeof(double) * dmd::solve_work_doubles(m, h->cplx));
-    ALLOC(h->Vfull, sizeof(double) * cw * (size_t)m * m);
+    if (!h->use_trid) ALLOC(h->Vfull, sizeof(double) * cw * (size_t)m * m);  // (all eigenvectors: Jacobi)
     ALLOC(h->Bphi, coef * 2 * (size_t)m * r);
     if (!h->cplx) {
         h->snap_B_bytes = (coef * 2 * (size_t)m * r + 255) / 256 * 256;
@@ -686,7 +688,7 @@ int create_impl(int64_t n, int32_t m, int32_t r, const dmd_opts_t* opts, dmd_str
         ALLOC(h->sh_At, sizeof(double) * ns * z.At);
         ALLOC(h->sh_W, sizeof(double) * ns * z.W);
         ALLOC(h->sh_work, sizeof(double) * ns * z.work);
-        ALLOC(h->sh_Vfull, sizeof(double) * ns * z.Vfull);
+        if (!h->use_trid) ALLOC(h->sh_Vfull, sizeof(double) * ns * z.Vfull);
         ALLOC(h->sh_Bphi, ns * z.Bphi);
         ALLOC(h->sh_Bpod, ns * z.Bpod);
         h->cfrag_elems = dmd::project_block_frag_bytes(m, r, h->kmax) / sizeof(uint4);
