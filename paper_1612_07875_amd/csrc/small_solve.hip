@@ -1308,22 +1308,15 @@ __device__ __forceinline__ int sturm_count(const double* __restrict__ d, const d
     return cnt;
 }
 
-template <typename S> __device__ __forceinline__ S shfl_xor_s(S v, int off, int width);
-template <> __device__ __forceinline__ double shfl_xor_s<double>(double v, int off, int width) {
-    return __shfl_xor(v, off, width);
-}
-template <> __device__ __forceinline__ cplx shfl_xor_s<cplx>(cplx v, int off, int width) {
+__device__ __forceinline__ cplx shfl_xor_c(cplx v, int off, int width) {
     return cplx{__shfl_xor(v.re, off, width), __shfl_xor(v.im, off, width)};
 }
-
-__device__ __forceinline__ double div_s(double a, double b) { return a / b; }
-__device__ __forceinline__ cplx div_s(cplx a, cplx b) { return cdiv(a, b); }
 
 // Householder reflector of column j (one wavefront): H = I - tau v v^* maps
 // x = A[j+1.., j] to (beta, 0, ..); v = (1, x[1..] / (alpha - beta)) is stored
 // over x[1..] and into vbuf, with tau, beta = e_j and d_j = A[j][j].
-template <typename S>
-__device__ void householder_col(S* A, int ld, int n, int j, S* vbuf, S* s_tau, double* s_e, double* s_d) {
+__device__ void householder_col(cplx* A, int ld, int n, int j, cplx* vbuf, cplx* s_tau, double* s_e, double* s_d) {
+    using S = cplx;
     using SC = Scal<S>;
     const int lane = threadIdx.x & 63;
     const int L = n - j - 1;
@@ -1341,7 +1334,7 @@ __device__ void householder_col(S* A, int ld, int n, int j, S* vbuf, S* s_tau, d
     if (!(xn2 == 0.0 && aa == ar)) {
         beta = -copysign(sqrt(aa * aa + xn2), ar);
         tau = (SC::fromc(mkc(beta)) - alpha) * (1.0 / beta);
-        scal = div_s(SC::one(), alpha - SC::fromc(mkc(beta)));
+        scal = cdiv(SC::one(), alpha - SC::fromc(mkc(beta)));
     }
     for (int i = 1 + lane; i < L; i += 64) {
         const S v = mulr(col[i], scal);
@@ -1356,8 +1349,9 @@ __device__ void householder_col(S* A, int ld, int n, int j, S* vbuf, S* s_tau, d
     }
 }
 
-template <typename S, int NT>
 __device__ void solve_trid_body(const SolveArgs& a) {
+    using S = cplx;
+    constexpr int NT = 1024;
     using SC = Scal<S>;
     extern __shared__ double dyn[];
     const int tid = threadIdx.x;
@@ -1409,7 +1403,7 @@ __device__ void solve_trid_body(const SolveArgs& a) {
     // c = -tau (p^* v) / 2.  Wavefront 0 updates the next column first and
     // builds its reflector while the others update the rest (two barriers
     // per column).  Row j+1 of A22 is never used again and is not updated.
-    if (wv == 0) householder_col<S>(A, ld, n, 0, s_v0, s_tau, s_e, s_d);
+    if (wv == 0) householder_col(A, ld, n, 0, s_v0, s_tau, s_e, s_d);
     __syncthreads();
     for (int j = 0; j + 1 < n; ++j) {
         const int L = n - j - 1;
@@ -1443,7 +1437,7 @@ __device__ void solve_trid_body(const SolveArgs& a) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (j + 2 < n) householder_col<S>(A, ld, n, j + 1, vnext, s_tau, s_e, s_d);
+            if (j + 2 < n) householder_col(A, ld, n, j + 1, vnext, s_tau, s_e, s_d);
         } else {
             // every element is read before the chunk's writes (no two
             // iterations touch the same element), so that the reads of a
@@ -1458,14 +1452,12 @@ __device__ void solve_trid_body(const SolveArgs& a) {
             auto at = [&](int idx) -> S& { return A22[(1 + idx % L1) + (size_t)(1 + idx / L1) * ld]; };
             constexpr int U = 4;
             int idx = tid - 64;
-            if constexpr (U > 1) {
-                for (; idx + (U - 1) * NW < L1 * L1; idx += U * NW) {
-                    S x[U];
+            for (; idx + (U - 1) * NW < L1 * L1; idx += U * NW) {
+                S x[U];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) x[u] = at(idx + u * NW);
+                for (int u = 0; u < U; ++u) x[u] = at(idx + u * NW);
 #pragma unroll
-                    for (int u = 0; u < U; ++u) at(idx + u * NW) = upd(idx + u * NW, x[u]);
-                }
+                for (int u = 0; u < U; ++u) at(idx + u * NW) = upd(idx + u * NW, x[u]);
             }
             for (; idx < L1 * L1; idx += NW) at(idx) = upd(idx, at(idx));
         }
@@ -1689,7 +1681,7 @@ __device__ void solve_trid_body(const SolveArgs& a) {
                     const S vi = i == 0 ? SC::one() : vj[i];
                     w = w + mulr(SC::cj(vi), zc[j + 1 + i]);
                 }
-                for (int off = 16; off >= 1; off >>= 1) w = w + shfl_xor_s<S>(w, off, 32);
+                for (int off = 16; off >= 1; off >>= 1) w = w + shfl_xor_c(w, off, 32);
                 const S f = mulr(tau, w);
                 for (int i = hl; i < L; i += 32) {
                     const S vi = i == 0 ? SC::one() : vj[i];
@@ -1711,12 +1703,12 @@ __device__ void solve_trid_body(const SolveArgs& a) {
 
 __global__ __launch_bounds__(1024)
 void k_solve_trid_wide(SolveArgs a) {
-    solve_trid_body<cplx, 1024>(a);
+    solve_trid_body(a);
 }
 __global__ __launch_bounds__(1024)
 void k_solve_trid_wide_grouped(const SolveArgs* __restrict__ items) {
     const SolveArgs a = items[blockIdx.x];
-    solve_trid_body<cplx, 1024>(a);
+    solve_trid_body(a);
 }
 
 }  // namespace

@@ -59,9 +59,10 @@ template <> __device__ __forceinline__ void store_s<cplx>(double* out, int64_t i
 }
 
 // 1/sqrt(x) to full FP64 accuracy: hardware estimate plus two Newton steps
-// (the estimate carries ~23 correct bits).  Dependent FP64 operations cost
-// ~32 cycles each here, so this replaces the longer correctly-rounded
-// sqrt/division sequences on the latency-bound paths.
+// (the estimate carries ~23 correct bits).  A dependent FP64 operation takes 6
+// cycles and any instruction about 4 of its wavefront's issue, so this replaces
+// the longer correctly rounded sqrt/division sequences on the latency-bound
+// paths.
 __device__ __forceinline__ double rsqrt_acc(double x) {
     double y = __builtin_amdgcn_rsq(x);
     const double h = 0.5 * x;

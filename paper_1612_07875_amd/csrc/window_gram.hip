@@ -3,9 +3,10 @@
 // of the bulk window load (k_gram_tiles + k_gram_reduce) run on a caller's
 // column-major matrix, writing the k x k FP64 result into a caller's buffer.
 //
-// The row-split partial tiles of the kernel (splits x upper-triangle tiles x
-// 64 x 64 FP64) are stream-ordered scratch: allocated with hipMallocAsync on
-// the caller's stream and freed after the reduction with hipFreeAsync.
+// The row ranges' partial tiles of the kernel (ranges x upper-triangle tiles of
+// 16 x 16 FP64, in an array sized by gram_full_tiles and gram_full_splits) are
+// stream-ordered scratch: allocated with hipMallocAsync on the caller's stream
+// and freed after the reduction with hipFreeAsync.
 //
 // The allocation-free variant (dmd_window_gram_noalloc) takes the partial
 // tiles from a fixed device array instead, sized for the largest window the
