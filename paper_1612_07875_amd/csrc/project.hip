@@ -11,7 +11,8 @@
 // and the window the B operand, so that a lane ends with the real and
 // imaginary parts of its rows and stores them from its registers.  A
 // wavefront owns 64 rows (four 16-row tiles) and all output columns (up to
-// four 16-column tiles).
+// four 16-column tiles).  Short windows take the window as the A operand
+// (project_body_direct).
 //
 // Fragment layouts of the 16x16x4 instructions (checked on the device):
 //   A: lane l holds A[l % 16][l / 16];  B: lane l holds B[l / 16][l % 16];
@@ -261,11 +262,11 @@ __device__ __forceinline__ void project_body(const ProjectArgs& a, int blk, T* c
 //
 // Where it is faster (us, this form and the one above, n = 2^20 unless named):
 // FP32, one column tile, m = 8, r = 2: 17 and 26, m = 24, r = 6: 38 and 41,
-// m = 40, r = 8 level, m = 64, r = 8: 77 and 77; two tiles, m = 12: 0.92, m = 16,
-// r = 16: 57 and 54; up to n = 131,072, where every workgroup runs at once, m <= 48
-// and up to three tiles (1 of 11 to 15 us).  FP64 data, one tile: m = 16, r = 8: 62 and
-// 80, m = 64: 143 and 158, m = 128: 250 and 265, m = 256 level; for n = 100,003
-// only to m = 32.  FP32 data in FP64 never (24 and 24 at m = 3; 62 and 54 at m = 8).
+// m = 64, r = 8: 77 and 77; two tiles, m = r = 12: 44 and 47, m = r = 16: 57 and
+// 54; up to n = 131,072, where every workgroup runs at once, m <= 48 and up to
+// three tiles (1 us of 11 to 15).  FP64 data, one tile, r = 8: m = 16: 62 and 80,
+// m = 64: 143 and 158, m = 128: 250 and 265, m = 256 level; for n = 100,003 only to
+// m = 32.  FP32 data in FP64 never (24 and 24 at m = 3; 62 and 54 at m = 8).
 template <typename TX, typename T> __host__ __device__ inline bool project_direct(int m, int nt, int64_t n) {
     if constexpr (sizeof(TX) == 8) return nt == 1 && (m <= 32 || (m <= 128 && n > 200000));
     else if constexpr (sizeof(T) == 8) return false;
