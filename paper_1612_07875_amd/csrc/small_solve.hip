@@ -513,7 +513,7 @@ void k_solve_sym_grouped(const SolveArgs* __restrict__ items) {
 // banks.
 //
 // Bound by the latency of those chains.  Against one wavefront with H and Z in
-// arrays of their own and b from a pivoted elimination of W Lambda: r = 10 real
+// arrays of their own and b always from a pivoted elimination: r = 10 real
 // 117 -> 64 us, r = 20 330 -> 163, r = 32 857 -> 349, r = 24 complex 685 -> 472;
 // 24 windows of a tick 878 -> 462.
 // --------------------------------------------------------------------------
@@ -832,11 +832,119 @@ struct EigShared {
         cplx hv[40];
     };
     cplx lam[kRMax], ls[kRMax];              // eigenvalues: Schur order, sorted
+    cplx al[kRMax];                          // POD coefficients alpha_1 of the first snapshot
     cplx x[kRMax];                           // expansion of alpha_1 in the unscaled eigenvectors
-    double mod[kRMax], arg[kRMax], sig[kRMax], isig[kRMax];
-    cplx fbg;
-    int bg, total, failed;
+    cplx b[kRMax];                           // mode amplitudes
+    int piv[kRMax];                          // pivot rows of the elimination for b
+    double mod[kRMax], arg[kRMax], isig[kRMax];
+    cplx fbg;                                // lambda_bg^m
+    int bg, total, failed, redo;
 };
+
+// Whether the amplitudes b reproduce the first snapshot with the published W
+// and lambda: |alpha_1 - W Lambda b| <= 64 eps |alpha_1|.  b comes from the
+// triangle of the Schur vectors, before pairs were made conjugate and columns
+// scaled.  A nearly defective A~ (a window with a linear trend) has nearly
+// parallel eigenvectors and large b that cancel, and those last changes to W then
+// cost up to the size of alpha_1 itself: such a window is solved again.
+__device__ __forceinline__ void check_amplitudes(EigShared& sh, int k) {
+    const int lane = threadIdx.x & 63, i = lane & 31, hf = lane >> 5;
+    if (lane < 32) sh.x[i] = i < k ? sh.ls[i] * sh.b[i] : mkc(0.0);
+    wave_sync();
+    cplx r = hf ? mkc(0.0) : sh.al[i] * -1.0;
+    for (int q0 = 16 * hf; q0 < 16 * hf + 16 && q0 < k; q0 += 4) {
+        cplx y[4], xx[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            y[u] = sh.Y[i + (q0 + u) * LDH];
+            xx[u] = sh.x[q0 + u];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) r = fmac(y[u], xx[u], r);
+    }
+    r = other_half_sum(r);
+    const double n2 = wave_sum(lane < k ? sqr(r) : 0.0), a2 = wave_sum(lane < k ? sqr(sh.al[i]) : 0.0);
+    if (lane == 0) sh.redo = !(n2 <= (64.0 * kEps) * (64.0 * kEps) * a2);
+}
+
+// b = (W Lambda)^-1 alpha_1 (Sec. 3.3) by Gaussian elimination with partial
+// pivoting on the published W and lambda.
+//
+// H over Z is free by now: its first rows take W Lambda.  Thread (i, g) keeps
+// the entries of row i in columns g, g + 8, .. in registers and copies them to
+// LDS, where a step reads column c and the pivot row; what it leaves in columns
+// up to c is not used again.  Rows stay in place; every wavefront finds the
+// pivot row by itself (32 bits hold the leading bits of an entry's square and
+// its row), so that a step has one barrier.  A zero pivot (an eigenvalue of
+// zero) gives its mode amplitude 0.  0.45 us a step.
+__device__ __forceinline__ void solve_amplitudes(EigShared& sh, int k) {
+    const int tid = threadIdx.x, lane = tid & 63, i = tid & 31, g = tid >> 5;
+    cplx* A = sh.M;
+    cplx own[4], rhs = mkc(0.0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int q = g + 8 * u;
+        own[u] = i < k && q < k ? sh.Y[i + q * LDH] * sh.ls[q] : mkc(0.0);
+        A[q * LDM + i] = own[u];
+    }
+    if (g == 0) {
+        rhs = sh.al[i];
+        sh.hv[i] = rhs;
+    }
+    __syncthreads();
+    bool free_row = i < k;
+    each_i<0, 4>([&](auto ph) {  // steps 8 ph .. 8 ph + 7: columns before 8 ph are done
+        const int end = 8 * ph() + 8 < k ? 8 * ph() + 8 : k;
+        for (int c = 8 * ph(); c < end; ++c) {
+            const cplx aic = A[c * LDM + i];
+            const unsigned hi = (unsigned)(__builtin_bit_cast(unsigned long long, abs2(aic)) >> 32);
+            unsigned key = free_row ? (hi & ~31u) | (unsigned)(31 - i) : 0u;
+            auto lvl = [&](auto ctrl) {
+                const unsigned o = (unsigned)__builtin_amdgcn_mov_dpp((int)key, decltype(ctrl)::value, 0xF, 0xF, true);
+                key = o > key ? o : key;
+            };
+            lvl(std::integral_constant<int, 0xB1>{});
+            lvl(std::integral_constant<int, 0x4E>{});
+            lvl(std::integral_constant<int, 0x141>{});
+            lvl(std::integral_constant<int, 0x140>{});
+            const auto sw = __builtin_amdgcn_permlane16_swap(key, key, false, false);
+            const int p = __builtin_amdgcn_readfirstlane(31 - (int)((sw[0] > sw[1] ? sw[0] : sw[1]) & 31u));
+            const cplx pv = A[c * LDM + p];
+            cplx top[4];
+            each_i<ph(), 4>([&](auto u) { top[u()] = A[(g + 8 * u()) * LDM + p]; });
+            const cplx rp = sh.hv[p];
+            if (tid == p) sh.piv[c] = p;
+            free_row = free_row && i != p;
+            const cplx f = div_fast(aic, pv) * -1.0;
+            if (free_row && abs2(pv) > 0.0) {
+                each_i<ph(), 4>([&](auto u) {
+                    own[u()] = fmac(f, top[u()], own[u()]);
+                    A[(g + 8 * u()) * LDM + i] = own[u()];
+                });
+                if (g == 0) {
+                    rhs = fmac(f, rp, rhs);
+                    sh.hv[i] = rhs;
+                }
+            }
+            __syncthreads();
+        }
+    });
+    if (tid < 64) {
+        const int l = i < k ? i : k - 1, p = sh.piv[l];
+        cplx r = sh.hv[p];
+        const cplx pv = A[l * LDM + p];
+        const cplx inv = abs2(pv) > 0.0 ? div_fast(mkc(1.0), pv) : mkc(0.0);
+        cplx cn = A[(k - 1) * LDM + p], b = mkc(0.0);
+        for (int c = k - 1; c >= 0; --c) {
+            const cplx cc = cn;
+            cn = A[(c > 0 ? c - 1 : 0) * LDM + p];
+            const cplx x = r * inv, xc = {lane_f64(x.re, c), lane_f64(x.im, c)};
+            if (l == c) b = xc;
+            if (l < c) r = fmac(cc * -1.0, xc, r);
+        }
+        if (lane < k) sh.b[lane] = b;
+    }
+}
 
 // C = V_r Sigma^-1 W: a thread keeps a row of V_r Sigma^-1 in registers, W
 // (sorted) is in LDS.  Windows of up to 64 (128) columns have four (two)
@@ -848,7 +956,7 @@ __device__ __forceinline__ void coef_rows(const SolveArgs& a, EigShared& sh, int
     using SC = Scal<S>;
     constexpr int U = sizeof(S) == sizeof(cplx) ? 2 : 4;  // rows of W read at a time (registers)
     const int ldv = a.m, bgq = sh.bg;
-    const cplx fbg = sh.fbg;
+    const cplx fbg = sh.b[bgq] * sh.fbg;
     const int parts = m <= 64 ? 4 : m <= 128 ? 2 : 1, rows = kEigThreads / parts;
     const int part = __builtin_amdgcn_readfirstlane(threadIdx.x / rows);
     for (int i = threadIdx.x % rows; i < m; i += rows) {
@@ -921,7 +1029,6 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a, EigShared& sh
     const int status0 = st->solve_status;
     const int k = st->r_eff;
     const int m = window_cols(a.m, a.buildup, st);  // columns of X
-    const int ldv = a.m;                            // leading dimension of V
     if (st->skipped) {
         publish(a);
         return;
@@ -950,8 +1057,13 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a, EigShared& sh
     }
     if (tid < kRMax) {
         const double sg = tid < k ? a.sigma[tid] : 1.0;
-        sh.sig[tid] = sg;
         sh.isig[tid] = 1.0 / sg;
+        cplx al = mkc(0.0);  // Sigma_r V_r^* e_1 (Sec. 3.3)
+        if (tid < k) {
+            const int64_t o = (int64_t)tid * a.m;
+            al = a.cplx ? sg * cplx{a.V[2 * o], -a.V[2 * o + 1]} : mkc(sg * a.V[o]);
+        }
+        sh.al[tid] = al;
     }
     __syncthreads();
     if (wave == 0) {
@@ -1010,25 +1122,17 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a, EigShared& sh
     }
     __syncthreads();
     // ---- W = Z Y over T (8 columns at a time), and meanwhile the expansion
-    // x = Y^-1 Z^* alpha_1 of the POD coefficients of the first snapshot,
-    // alpha_1 = Sigma_r V_r^* e_1 (Sec. 3.3), in the columns of Z Y
+    // x = Y^-1 Z^* alpha_1 of the first snapshot's coefficients in the columns
+    // of Z Y
     if (wave == 3) {
         const int q = lane & 31, hf = lane >> 5;
-        cplx al = mkc(0.0);
-        if (q < k) {
-            const cplx v0 = a.cplx ? cplx{a.V[2 * ((int64_t)q * ldv)], a.V[2 * ((int64_t)q * ldv) + 1]}
-                                   : mkc(a.V[(int64_t)q * ldv]);
-            al = sh.sig[q] * conj(v0);
-        }
-        if (lane < 32) sh.x[q] = al;
-        wave_sync();
         cplx g = mkc(0.0);
         for (int i = 16 * hf; i < 16 * hf + 16; i += 4) {
             cplx zz[4], xx[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 zz[u] = conj(sh.M[q * LDM + 32 + i + u]);
-                xx[u] = sh.x[i + u];
+                xx[u] = sh.al[i + u];
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) g = fmac(zz[u], xx[u], g);
@@ -1174,9 +1278,7 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a, EigShared& sh
                 sh.ls[rank] = lq;
                 a.lam[2 * rank] = lq.re;
                 a.lam[2 * rank + 1] = lq.im;
-                const cplx b = cdiv(sh.x[q], scale_q * lq);
-                a.amp[2 * rank] = b.re;
-                a.amp[2 * rank + 1] = b.im;
+                sh.b[rank] = cdiv(sh.x[q], scale_q * lq);
             }
         }
     }
@@ -1214,10 +1316,20 @@ __device__ __forceinline__ void solve_eig_body(const SolveArgs& a, EigShared& sh
             // lambda^m = |lambda|^m e^{i m arg lambda}
             const cplx lb = sh.ls[bi];
             const double pm = pow(cabs(lb), (double)m), th = (double)m * atan2(lb.im, lb.re);
-            sh.fbg = cplx{a.amp[2 * bi], a.amp[2 * bi + 1]} * cplx{pm * cos(th), pm * sin(th)};
+            sh.fbg = cplx{pm * cos(th), pm * sin(th)};
         }
+    } else if (wave == 1) {
+        check_amplitudes(sh, k);
     }
     __syncthreads();
+    if (sh.redo) {
+        solve_amplitudes(sh, k);
+        __syncthreads();
+    }
+    if (tid < k) {
+        a.amp[2 * tid] = sh.b[tid].re;
+        a.amp[2 * tid + 1] = sh.b[tid].im;
+    }
     // ---- C = V_r Sigma^-1 W (m x k complex), row-major with row stride 2 r
     if (a.cplx) coef_rows<cplx>(a, sh, m, k);
     else coef_rows<double>(a, sh, m, k);
