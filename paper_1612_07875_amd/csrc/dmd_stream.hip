@@ -1985,7 +1985,7 @@ int batch_tick_impl(dmd_batch* b, int count, dmd_stream* const* streams, const T
     // (m > 64) first, on the side stream from their solves on, the others
     // behind their Gram pass on the tick's stream.  The solves keep a workgroup
     // per window busy and leave the memory idle: a wide window's
-    // (reduction, values, vectors and eig in turn, about 700 us at m = 128, r =
+    // (reduction, values, vectors and eig in turn, about 750 us at m = 128, r =
     // 32) run beside the other members' Gram pass and solves; its projection
     // waits for that Gram pass (no modes are written before every frame is
     // read).  One chain where

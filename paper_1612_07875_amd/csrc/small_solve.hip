@@ -514,8 +514,8 @@ void k_solve_sym_grouped(const SolveArgs* __restrict__ items) {
 //
 // Bound by the latency of those chains.  Against one wavefront with H and Z in
 // arrays of their own and b always from a pivoted elimination: r = 10 real
-// 117 -> 64 us, r = 20 330 -> 163, r = 32 857 -> 349, r = 24 complex 685 -> 472;
-// 24 windows of a tick 878 -> 462.
+// 117 -> 66 us, r = 20 330 -> 169, r = 32 857 -> 362, r = 24 complex 685 -> 471;
+// 24 windows of a tick 878 -> 419.
 // --------------------------------------------------------------------------
 constexpr int LDM = 65;
 constexpr int kEigCols = 39;  // 32, and the (zero) columns that a run of eight may reach past them
@@ -627,9 +627,9 @@ __device__ __forceinline__ int deflate(S* M, int hi, int lane, double hmax) {
 // (x + sign(x) s, y, z), s = ||(x, y, z)||, tau = 2 / u^T u, by the
 // hardware estimates plus Newton steps), the three rows (lane = column), LDS,
 // the three columns (lane = row of H or Z), and the next (x, y, z) from the
-// lanes that hold them.  22 sweeps of a 20 x 20 matrix take 68 us, deflation
-// checks included (about 700 cycles a step); with the rows of Z apart from H's,
-// masked writes and 2 / v^T v summed up a step took 1000 to 1200.
+// lanes that hold them.  22 sweeps of a 20 x 20 matrix take about 73 us,
+// deflation checks included (about 750 cycles a step); with the rows of Z apart
+// from H's and masked writes a step took 1000 to 1200.
 __device__ __forceinline__ void real_schur(double* M, int k, int lane, int max_iter, double hmax, int& total,
                                            bool& failed) {
     auto h = [&](int i, int j) -> double& { return M[j * LDM + i]; };
@@ -950,7 +950,7 @@ __device__ __forceinline__ void solve_amplitudes(EigShared& sh, int k) {
 // (sorted) is in LDS.  Windows of up to 64 (128) columns have four (two)
 // threads for a row, each with its share of the columns of C; several rows of W for two
 // columns are read at a time.  With a thread per row, complex rows for real V and
-// one row of W at a time it took 26 us of the solve's 189 (m = 64, r = 20), now 163 in all.
+// one row of W at a time it took 26 us of the solve's 189 (m = 64, r = 20), now 169 in all.
 template <typename S>
 __device__ __forceinline__ void coef_rows(const SolveArgs& a, EigShared& sh, int m, int k) {
     using SC = Scal<S>;

@@ -16,10 +16,10 @@
 //
 // Measured on an MI355X, one window, reduction + values + vectors, against the
 // solve by one 1024-thread workgroup that they replace (matrix in LDS to
-// m = 64 real, else in the workspace): m = 32, r = 10: 21 + 10 + 12 us, was 119
-// (both with the finalize); m = 64, r = 20: 51 + 17 + 25, was 294; m = 120,
-// r = 15: 119 + 30 + 50, was 781; m = 256, r = 32: 609 + 59 + 170, was 3951;
-// Hermitian m = 128, r = 24: 263 + 32 + 100, was 1209.  Hermitian windows of
+// m = 64 real, else in the workspace): m = 32, r = 10: 20 + 10 + 14 us, was 119;
+// m = 64, r = 20: 50 + 18 + 25, was 294; m = 120, r = 15: 117 + 32 + 50, was
+// 781 (these with the finalize); m = 256, r = 32: 619 + 63 + 203, was 3951;
+// Hermitian m = 128, r = 24: 262 + 34 + 95, was 1209.  Hermitian windows of
 // more than 128 columns exceed the registers and keep the one-workgroup solve.
 #include <type_traits>
 
