@@ -860,7 +860,7 @@ DMD_API int dmd_stream_push(dmd_stream_t* h, const void* x, void* stream) {
                                                h->n, h->m, h->slots, h->partials, h->nblk_cap, st, h->gram_iter,
                                                &nblk, s);
     });
-    // with the tridiagonal solver the finalize and the solve are one launch
+    // with the tridiagonal solver the finalize and the reduction are one launch (m <= 128)
     const bool fuse = h->opts.auto_solve && h->use_trid;
     if (e == hipSuccess && !fuse)
         e = timed("gram_finalize", s,

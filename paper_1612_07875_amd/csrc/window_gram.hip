@@ -58,9 +58,9 @@ hipError_t launch_window_gram(const void* X, int64_t ldx, int64_t n, int32_t nco
     return launch_gram_full(X, ldx, n, ncols - 1, (int)ldg, elem_f64, precision, ncols, 0, partial, G, nullptr, 0, s);
 }
 
-// Scratch of the allocation-free call: the partial tiles of the largest window
-// (257 columns: 15 upper-triangle tiles x 35 row splits; no smaller window
-// needs more), one copy per device, held until the process ends.  Every
+// Scratch of the allocation-free call, in units of 64 x 64: every window length
+// asks for gram_full_tiles x gram_full_splits of them, 480 at most (257
+// columns: 15 x 32), one copy per device, held until the process ends.  Every
 // partial tile is written in full by each call, so nothing needs clearing.
 // Host code never uses this name as an address: the device address comes
 // from noalloc_scratch() below.
